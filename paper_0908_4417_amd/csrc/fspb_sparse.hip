@@ -7,17 +7,17 @@
  *     k_fluence_gradient  g_j = sum_i D_ij r_i, fixed order      -- one workgroup per row
  *   voxel-row CSR (row i = voxel, columns = beamlets): the transpose, a stable
  *   sort of the row-major entries by column
- *     k_run_count, scan, k_run_sizes   runs of each row (stretches within one
- *                                      32-column bucket), their pointers, the
+ *     k_run_count, scan, k_run_sizes   runs of each piece of a row (stretches within
+ *                                      one 32-column bucket), their pointers, the
  *                                      path flags
  *     run path (the default for D, whose rows are long stretches of columns):
  *       k_run_emit                     run records: bucket, row, first entry and a
  *                                      32-bit column mask (ascending rows) or length
- *       k_rs_hist, scan, k_rs_scatter  stable LSD radix sort of the runs by bucket
+ *       k_rs_hist, scan, k_run_scatter stable LSD radix sort of the runs by bucket
  *       k_bucket_bounds                bucket pointers
- *       rows ascending:   scan of the lengths, k_place_sorted -- one wave per
- *                         bucket: column counts from the masks (the voxel-row
- *                         pointers), batches reordered in LDS and written out
+ *       rows ascending:   k_bucket_count (column counts from the masks), scan (the
+ *                         voxel-row pointers), k_place_sorted -- runs' values in
+ *                         registers by column, written out column by column
  *       rows in any order: k_key_count + scan (pointers), k_place_any
  *     entry path (short stretches): k_key_count + scan, k_expand_rows, then
  *       k_rs_hist, scan, k_rs_scatter per 8 bits of the column
@@ -32,6 +32,7 @@
 
 #include <algorithm>
 #include <mutex>
+#include <utility>
 
 #include "fspb_device.h"
 
@@ -42,14 +43,16 @@ namespace {
 constexpr int kBlock = 256;
 constexpr int kWavesPerBlock = kBlock / kWave;
 constexpr int kRadixBits = 8;
-constexpr int kRadix = 1 << kRadixBits;          // digits per pass; one thread per digit
-constexpr int kSortItems = 16;                   // items per thread per tile
-constexpr int kSortTile = kBlock * kSortItems;   // 4096 entries per sort tile
-constexpr int kScanItems = 16;
-constexpr int kScanChunk = kBlock * kScanItems;  // 4096 values per scan block
+constexpr int kRadix = 1 << kRadixBits;          // digits per pass
+constexpr int kSortBlock = 512;                  // threads of a scatter workgroup
+constexpr int kSortWaves = kSortBlock / kWave;
+constexpr int kSortItems = 8;                    // entries per thread of a tile
+constexpr int kSortTile = kSortBlock * kSortItems;   // 4096 entries per sort tile
+constexpr int kScanRounds = 4;
+constexpr int kScanChunk = 4 * kBlock * kScanRounds;   // 4096 values per scan block
 constexpr int kScanTop = 1024;
 
-static_assert(kRadix == kBlock, "one thread per digit");
+static_assert(kRadix == kBlock && kRadix <= kSortBlock, "one thread per digit");
 
 __device__ inline int lane_id() { return threadIdx.x & (kWave - 1); }
 
@@ -91,7 +94,8 @@ __device__ inline uint32_t wave_sum(uint32_t x)
     return (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_scan(x), kWave - 1);
 }
 
-/* Exclusive scan of one value per thread over the block; *total gets the sum. */
+/* Exclusive scan of one value per thread over a block of W waves; *total gets the sum. */
+template <int W = kWavesPerBlock>
 __device__ inline uint32_t block_excl_scan(uint32_t v, uint32_t *s_w, uint32_t *total)
 {
     const int l = lane_id(), w = threadIdx.x >> 6;
@@ -100,7 +104,7 @@ __device__ inline uint32_t block_excl_scan(uint32_t v, uint32_t *s_w, uint32_t *
     __syncthreads();
     uint32_t off = 0, tot = 0;
 #pragma unroll
-    for (int k = 0; k < kWavesPerBlock; ++k) {
+    for (int k = 0; k < W; ++k) {
         const uint32_t t = s_w[k];
         off += k < w ? t : 0u;
         tot += t;
@@ -548,9 +552,15 @@ __global__ __launch_bounds__(kBlock) void k_expand_rows(const int64_t *__restric
     for (int64_t e = e0 + lane_id(); e < e1; e += kWave) rows[e] = j;
 }
 
-/* Scan, phase 1: sum of each kScanChunk-value chunk (grid-stride over chunks); with
- * POPC the values scanned are the popcounts of the inputs (here and in phase 3). */
-template <bool POPC>
+/* Values base .. base + 3 of in[0, n), 0 past the end (in: 16-byte aligned, base a multiple of 4). */
+__device__ inline uint4 load_four(const uint32_t *in, int64_t base, int64_t n)
+{
+    if (base + 3 < n) return *reinterpret_cast<const uint4 *>(in + base);
+    return make_uint4(base < n ? in[base] : 0u, base + 1 < n ? in[base + 1] : 0u, base + 2 < n ? in[base + 2] : 0u, 0u);
+}
+
+/* Scan, phase 1: sum of each kScanChunk-value chunk (grid-stride over chunks).  In both this and
+ * phase 3 a thread takes four consecutive values a round, so that a wave reads 1 KB in one go. */
 __global__ __launch_bounds__(kBlock) void k_scan_reduce(const uint32_t *__restrict__ in, Count n_in,
                                                         uint32_t *__restrict__ partial, Gate g)
 {
@@ -558,12 +568,11 @@ __global__ __launch_bounds__(kBlock) void k_scan_reduce(const uint32_t *__restri
     __shared__ uint32_t s_w[kWavesPerBlock];
     const int64_t n = count_of(n_in), nch = (n + kScanChunk - 1) / kScanChunk;
     for (int64_t c = blockIdx.x; c < nch; c += gridDim.x) {
-        const int64_t base = c * kScanChunk + (int64_t)threadIdx.x * kScanItems;
         uint32_t v = 0;
 #pragma unroll
-        for (int k = 0; k < kScanItems; ++k) {
-            const uint32_t x = base + k < n ? in[base + k] : 0u;
-            v += POPC ? (uint32_t)__popc(x) : x;
+        for (int r = 0; r < kScanRounds; ++r) {
+            const uint4 x = load_four(in, c * kScanChunk + (r * kBlock + (int)threadIdx.x) * 4, n);
+            v += x.x + x.y + x.z + x.w;
         }
         v = wave_sum(v);
         if (lane_id() == 0) s_w[threadIdx.x >> 6] = v;
@@ -608,9 +617,9 @@ __global__ __launch_bounds__(kScanTop) void k_scan_top(uint32_t *__restrict__ pa
     }
 }
 
-/* Scan, phase 3: exclusive (INCL: inclusive) scan within each chunk plus its chunk
- * offset (grid-stride); out may be in (each chunk is read before it is written). */
-template <typename OUT, bool INCL, bool POPC>
+/* Scan, phase 3: exclusive scan within each chunk plus its chunk offset (grid-stride); out may
+ * be in (each round is read before it is written). */
+template <typename OUT>
 __global__ __launch_bounds__(kBlock) void k_scan_down(const uint32_t *in, Count n_in, const uint32_t *__restrict__ partial,
                                                       OUT *out, Gate g)
 {
@@ -618,22 +627,21 @@ __global__ __launch_bounds__(kBlock) void k_scan_down(const uint32_t *in, Count 
     __shared__ uint32_t s_w[kWavesPerBlock];
     const int64_t n = count_of(n_in), nch = (n + kScanChunk - 1) / kScanChunk;
     for (int64_t c = blockIdx.x; c < nch; c += gridDim.x) {
-        const int64_t base = c * kScanChunk + (int64_t)threadIdx.x * kScanItems;
-        uint32_t v[kScanItems];
-        uint32_t sum = 0;
+        uint32_t run = partial[c];
+        uint4 x[kScanRounds];
 #pragma unroll
-        for (int k = 0; k < kScanItems; ++k) {
-            v[k] = base + k < n ? in[base + k] : 0u;
-            if (POPC) v[k] = (uint32_t)__popc(v[k]);
-            sum += v[k];
-        }
-        uint32_t total;
-        uint32_t run = partial[c] + block_excl_scan(sum, s_w, &total);
+        for (int r = 0; r < kScanRounds; ++r)
+            x[r] = load_four(in, c * kScanChunk + (r * kBlock + (int)threadIdx.x) * 4, n);
 #pragma unroll
-        for (int k = 0; k < kScanItems; ++k) {
-            run += INCL ? v[k] : 0u;
-            if (base + k < n) out[base + k] = (OUT)run;
-            run += INCL ? 0u : v[k];
+        for (int r = 0; r < kScanRounds; ++r) {
+            const int64_t i = c * kScanChunk + (r * kBlock + (int)threadIdx.x) * 4;
+            uint32_t total;
+            const uint32_t e = run + block_excl_scan(x[r].x + x[r].y + x[r].z + x[r].w, s_w, &total);
+            run += total;
+            if (i < n) out[i] = (OUT)e;
+            if (i + 1 < n) out[i + 1] = (OUT)(e + x[r].x);
+            if (i + 2 < n) out[i + 2] = (OUT)(e + x[r].x + x[r].y);
+            if (i + 3 < n) out[i + 3] = (OUT)(e + x[r].x + x[r].y + x[r].z);
         }
     }
 }
@@ -641,7 +649,9 @@ __global__ __launch_bounds__(kBlock) void k_scan_down(const uint32_t *in, Count 
 /* Radix pass, phase 1: digit histogram of each kSortTile-entry tile, stored
  * digit-major (hist[d * n_tiles + tile]) so that one exclusive scan gives every
  * (digit, tile) its first output slot.  Keys above `clamp` count as `clamp`
- * (the sentinel that sorts entries with an invalid column last). */
+ * (the sentinel that sorts entries with an invalid column last).  Keys lie
+ * STRIDE words apart. */
+template <int STRIDE>
 __global__ __launch_bounds__(kBlock) void k_rs_hist(const uint32_t *__restrict__ keys, Count n_in, uint32_t clamp,
                                                     int shift, uint32_t *__restrict__ hist, Gate g)
 {
@@ -652,10 +662,10 @@ __global__ __launch_bounds__(kBlock) void k_rs_hist(const uint32_t *__restrict__
         h[threadIdx.x] = 0u;
         __syncthreads();
         const int64_t base = tile * kSortTile + threadIdx.x;
-#pragma unroll 4
-        for (int r = 0; r < kSortItems; ++r) {
+#pragma unroll
+        for (int r = 0; r < kSortTile / kBlock; ++r) {
             const int64_t i = base + (int64_t)r * kBlock;
-            if (i < n) atomicAdd(&h[(min(keys[i], clamp) >> shift) & (kRadix - 1)], 1u);
+            if (i < n) atomicAdd(&h[(min(keys[i * STRIDE], clamp) >> shift) & (kRadix - 1)], 1u);
         }
         __syncthreads();
         hist[(int64_t)threadIdx.x * n_tiles + tile] = h[threadIdx.x];
@@ -664,47 +674,90 @@ __global__ __launch_bounds__(kBlock) void k_rs_hist(const uint32_t *__restrict__
 }
 
 /*
- * Radix pass, phase 2: stable scatter (of a fourth uint32 payload too with XTRA).  Wave w of a block owns the w-th
- * quarter of the tile (kSortItems rounds of 64 consecutive entries) and
- * ranks it on its own: in a round, ballots on the 8 digit bits group the
- * lanes holding the same digit, a lane's rank is the number of lower peers,
- * and the wave's per-digit counter in LDS (read by the group, advanced by its
- * lowest lane) orders the rounds.  The entries stay in registers; one block
- * scan turns the waves' counts into tile-local slots (digit-major, lower
- * waves first), the tile is sorted by digit in LDS and written out in that
- * order, so each digit's run goes to consecutive addresses.  keys_out may be
- * NULL (last pass).  Grid-stride over the tiles.
+ * Radix pass, phase 2: stable scatter of a tile.  Wave w of a block owns the
+ * w-th part of the tile (kSortItems rounds of 64 consecutive entries) and ranks
+ * it on its own: in a round, ballots on the 8 digit bits group the lanes
+ * holding the same digit, a lane's rank is the number of lower peers, and the
+ * wave's per-digit counter in LDS (read by the group, advanced by its lowest
+ * lane) orders the rounds.  One block scan turns the waves' counts into
+ * tile-local slots (digit-major, lower waves first): slot[] on return, and
+ * goff[d] the global slot of tile-local slot 0 of digit d's run.
  */
-template <bool XTRA>
-__global__ __launch_bounds__(kBlock) void k_rs_scatter(const uint32_t *__restrict__ keys_in,
-                                                       const int32_t *__restrict__ rows_in,
-                                                       const float *__restrict__ vals_in,
-                                                       const uint32_t *__restrict__ xs_in, Count n_in, uint32_t clamp,
-                                                       int shift, const uint32_t *__restrict__ offs,
-                                                       uint32_t *__restrict__ keys_out,
-                                                       int32_t *__restrict__ rows_out,
-                                                       float *__restrict__ vals_out, uint32_t *__restrict__ xs_out,
-                                                       Gate g)
+struct TileRank {
+    uint32_t cnt[kSortWaves][kRadix];   // per wave: digit counts, then first tile-local slot
+    uint32_t goff[kRadix];
+    uint32_t w[kSortWaves];
+};
+
+__device__ inline void rank_tile(TileRank &T, const uint32_t (&key)[kSortItems], int64_t sub0, int64_t n, int shift,
+                                 const uint32_t *__restrict__ offs, int64_t n_tiles, int64_t tile,
+                                 uint32_t (&slot)[kSortItems])
+{
+    const int t = threadIdx.x, wave = t >> 6, lane = t & (kWave - 1);
+    for (int k = t; k < kSortWaves * kRadix; k += kSortBlock) (&T.cnt[0][0])[k] = 0u;
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < kSortItems; ++r) {
+        const bool valid = sub0 + (int64_t)r * kWave + lane < n;
+        const uint32_t d = (key[r] >> shift) & (kRadix - 1);
+        uint64_t peers = __ballot(valid);
+#pragma unroll
+        for (int b = 0; b < kRadixBits; ++b) {
+            const bool bit = (d >> b) & 1u;
+            const uint64_t m = __ballot(bit);
+            peers &= bit ? m : ~m;
+        }
+        const uint32_t rank = (uint32_t)mbcnt64(peers);
+        uint32_t before = 0u;
+        if (valid) before = T.cnt[wave][d];                 // every lane of the group reads the old count
+        if (valid && rank == 0) T.cnt[wave][d] = before + (uint32_t)__popcll(peers);
+        slot[r] = before + rank;
+    }
+    __syncthreads();
+    // thread t < kRadix = digit t: tile-local start of the digit, then of each wave's part of it
+    uint32_t c[kSortWaves], tot = 0;
+#pragma unroll
+    for (int w = 0; w < kSortWaves; ++w) {
+        c[w] = t < kRadix ? T.cnt[w][t] : 0u;
+        tot += c[w];
+    }
+    uint32_t total;
+    const uint32_t start = block_excl_scan<kSortWaves>(tot, T.w, &total);
+    if (t < kRadix) {
+        uint32_t b = start;
+#pragma unroll
+        for (int w = 0; w < kSortWaves; ++w) {
+            T.cnt[w][t] = b;
+            b += c[w];
+        }
+        T.goff[t] = offs[(int64_t)t * n_tiles + tile] - start;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < kSortItems; ++r) slot[r] += T.cnt[wave][(key[r] >> shift) & (kRadix - 1)];
+}
+
+/* Scatter of (key, row, value) entries: the tile is sorted by digit in LDS, the
+ * values after the keys and rows, and written out in that order, so each
+ * digit's run goes to consecutive addresses.  keys_out may be NULL (last pass).
+ * Grid-stride over the tiles. */
+__global__ __launch_bounds__(kSortBlock) void k_rs_scatter(const uint32_t *__restrict__ keys_in,
+                                                           const int32_t *__restrict__ rows_in,
+                                                           const float *__restrict__ vals_in, Count n_in,
+                                                           uint32_t clamp, int shift,
+                                                           const uint32_t *__restrict__ offs,
+                                                           uint32_t *__restrict__ keys_out,
+                                                           int32_t *__restrict__ rows_out,
+                                                           float *__restrict__ vals_out, Gate g)
 {
     if (gate_closed(g)) return;
-    __shared__ uint32_t s_key[kSortTile];
-    __shared__ int32_t s_row[kSortTile];
-    __shared__ float s_val[kSortTile];
-    __shared__ uint32_t s_x[XTRA ? kSortTile : 1];
-    __shared__ uint32_t cnt[kWavesPerBlock][kRadix];   // per wave: digit counts, then first tile-local slot
-    __shared__ uint32_t goff[kRadix];                  // global slot of tile-local slot 0 of each digit's run
-    __shared__ uint32_t s_w[kWavesPerBlock];
-    constexpr int kSub = kSortTile / kWavesPerBlock;    // entries per wave
-    const int t = threadIdx.x, wave = t >> 6, lane = t & (kWave - 1);
+    __shared__ uint2 s_pair[kSortTile];
+    __shared__ TileRank T;
+    const int t = threadIdx.x, lane = t & (kWave - 1);
     const int64_t n = count_of(n_in), n_tiles = (n + kSortTile - 1) / kSortTile;
     for (int64_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
-        const int64_t tile0 = tile * kSortTile;
-        const int64_t sub0 = tile0 + (int64_t)wave * kSub;
-#pragma unroll
-        for (int w = 0; w < kWavesPerBlock; ++w) cnt[w][t] = 0u;
-        __syncthreads();
-
-        uint32_t key[kSortItems], pos[kSortItems], xv[kSortItems];
+        const int64_t tile0 = tile * kSortTile, sub0 = tile0 + (int64_t)(t >> 6) * (kSortTile / kSortWaves);
+        uint32_t key[kSortItems], slot[kSortItems], at[kSortItems];
         int32_t row[kSortItems];
         float val[kSortItems];
 #pragma unroll
@@ -714,62 +767,74 @@ __global__ __launch_bounds__(kBlock) void k_rs_scatter(const uint32_t *__restric
             key[r] = valid ? min(keys_in[i], clamp) : 0u;
             row[r] = valid ? rows_in[i] : 0;
             val[r] = valid ? vals_in[i] : 0.0f;
-            xv[r] = (XTRA && valid) ? xs_in[i] : 0u;
-            const uint32_t d = (key[r] >> shift) & (kRadix - 1);
-            uint64_t peers = __ballot(valid);
+        }
+        rank_tile(T, key, sub0, n, shift, offs, n_tiles, tile, slot);
 #pragma unroll
-            for (int b = 0; b < kRadixBits; ++b) {
-                const bool bit = (d >> b) & 1u;
-                const uint64_t m = __ballot(bit);
-                peers &= bit ? m : ~m;
+        for (int r = 0; r < kSortItems; ++r)
+            if (sub0 + (int64_t)r * kWave + lane < n) s_pair[slot[r]] = make_uint2(key[r], (uint32_t)row[r]);
+        __syncthreads();
+        const int m = (int)min((int64_t)kSortTile, n - tile0);
+#pragma unroll
+        for (int r = 0; r < kSortItems; ++r) {
+            const int lp = r * kSortBlock + t;
+            if (lp < m) {
+                const uint2 q = s_pair[lp];
+                at[r] = T.goff[(q.x >> shift) & (kRadix - 1)] + (uint32_t)lp;
+                if (keys_out) keys_out[at[r]] = q.x;
+                rows_out[at[r]] = (int32_t)q.y;
             }
-            const uint32_t rank = (uint32_t)mbcnt64(peers);
-            uint32_t before = 0u;
-            if (valid) before = cnt[wave][d];                 // every lane of the group reads the old count
-            if (valid && rank == 0) cnt[wave][d] = before + (uint32_t)__popcll(peers);
-            pos[r] = before + rank;
         }
         __syncthreads();
-        {
-            // thread t = digit t: tile-local start of the digit, then of each wave's part of it
-            uint32_t c[kWavesPerBlock], tot = 0;
 #pragma unroll
-            for (int w = 0; w < kWavesPerBlock; ++w) {
-                c[w] = cnt[w][t];
-                tot += c[w];
-            }
-            uint32_t total;
-            const uint32_t start = block_excl_scan(tot, s_w, &total);
-            uint32_t b = start;
-#pragma unroll
-            for (int w = 0; w < kWavesPerBlock; ++w) {
-                cnt[w][t] = b;
-                b += c[w];
-            }
-            goff[t] = offs[(int64_t)t * n_tiles + tile] - start;
-        }
+        for (int r = 0; r < kSortItems; ++r)
+            if (sub0 + (int64_t)r * kWave + lane < n) s_pair[slot[r]].x = __float_as_uint(val[r]);
         __syncthreads();
 #pragma unroll
         for (int r = 0; r < kSortItems; ++r) {
-            const int64_t i = sub0 + (int64_t)r * kWave + lane;
-            if (i < n) {
-                const uint32_t lp = cnt[wave][(key[r] >> shift) & (kRadix - 1)] + pos[r];
-                s_key[lp] = key[r];
-                s_row[lp] = row[r];
-                s_val[lp] = val[r];
-                if (XTRA) s_x[lp] = xv[r];
-            }
+            const int lp = r * kSortBlock + t;
+            if (lp < m) vals_out[at[r]] = __uint_as_float(s_pair[lp].x);
         }
         __syncthreads();
-        const int64_t rem = n - tile0;
-        const int m = rem < kSortTile ? (int)rem : kSortTile;
-        for (int lp = t; lp < m; lp += kBlock) {
-            const uint32_t key_ = s_key[lp];
-            const uint32_t p = goff[(key_ >> shift) & (kRadix - 1)] + (uint32_t)lp;
-            if (keys_out) keys_out[p] = key_;
-            rows_out[p] = s_row[lp];
-            vals_out[p] = s_val[lp];
-            if (XTRA) xs_out[p] = s_x[lp];
+    }
+}
+
+/* A run of the transpose: bucket key, row (flagged when invalid), first entry, auxiliary word. */
+typedef uint4 Run;
+
+/*
+ * Scatter of run records, 16 bytes each: a digit's run of a tile (16 records on
+ * average) is 256 contiguous bytes, where four separate arrays were written in
+ * pieces of 64, each parts of two cache lines (3.7e7 runs: 0.30 ms a pass against
+ * 0.49).
+ */
+__global__ __launch_bounds__(kSortBlock) void k_run_scatter(const Run *__restrict__ in, Count n_in, int shift,
+                                                            const uint32_t *__restrict__ offs, Run *__restrict__ out,
+                                                            Gate g)
+{
+    if (gate_closed(g)) return;
+    __shared__ Run s_run[kSortTile];
+    __shared__ TileRank T;
+    const int t = threadIdx.x, lane = t & (kWave - 1);
+    const int64_t n = count_of(n_in), n_tiles = (n + kSortTile - 1) / kSortTile;
+    for (int64_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
+        const int64_t tile0 = tile * kSortTile, sub0 = tile0 + (int64_t)(t >> 6) * (kSortTile / kSortWaves);
+        Run run[kSortItems];
+        uint32_t key[kSortItems], slot[kSortItems];
+#pragma unroll
+        for (int r = 0; r < kSortItems; ++r) {
+            const int64_t i = sub0 + (int64_t)r * kWave + lane;
+            run[r] = i < n ? in[i] : make_uint4(0u, 0u, 0u, 0u);
+            key[r] = run[r].x;
+        }
+        rank_tile(T, key, sub0, n, shift, offs, n_tiles, tile, slot);
+#pragma unroll
+        for (int r = 0; r < kSortItems; ++r)
+            if (sub0 + (int64_t)r * kWave + lane < n) s_run[slot[r]] = run[r];
+        __syncthreads();
+        const int m = (int)min((int64_t)kSortTile, n - tile0);
+        for (int lp = t; lp < m; lp += kSortBlock) {
+            const Run q = s_run[lp];
+            out[T.goff[(q.x >> shift) & (kRadix - 1)] + (uint32_t)lp] = q;
         }
         __syncthreads();
     }
@@ -847,9 +912,8 @@ constexpr uint32_t kRunFlag = 0x80000000u;   // run of invalid columns (in the r
 constexpr int kRowChunks = 4;                // chunks of 64 entries whose loads are in flight together
 constexpr int kXcds = 8;                     // workgroups are handed to the 8 XCDs in turn
 
-/* Value of the lane below (above), through a whole-wave DPP shift; lane 0 (63) takes `edge`. */
+/* Value of the lane below, through a whole-wave DPP shift; lane 0 takes `edge`. */
 __device__ inline int from_lane_below(int v, int edge) { return __builtin_amdgcn_update_dpp(edge, v, 0x138, 0xf, 0xf, false); }
-__device__ inline int from_lane_above(int v, int edge) { return __builtin_amdgcn_update_dpp(edge, v, 0x130, 0xf, 0xf, false); }
 
 /* Run key of a column: its bucket, or -2 (outside [0, n_voxels)). */
 __device__ inline int run_key(int col, int n_voxels)
@@ -865,9 +929,37 @@ struct Flags {
     int32_t need_counts;   // entries per column counted by atomics (entry path, unsorted rows)
     int32_t sorted;        // run path with masks (rows ascending)
     int32_t any;           // run path for rows in any column order
-    int32_t pad;
-    int64_t total;         // placed entries (sorted run path)
+    int32_t pad[9];
 };
+static_assert(sizeof(Flags) == 64, "one slot");
+
+/*
+ * The rows in pieces of equal length, `split` of them to a row (more than one where the rows are
+ * too few to fill the chip), one wave each.  A piece is read in blocks of kRunBlock entries, and
+ * its first entry and each block's start a run of their own (one in a thousand entries): no run
+ * is open where a wave begins to read.
+ */
+constexpr int kRunSteps = 16;
+constexpr int kRunBlock = kRunSteps * kWave;
+
+struct Piece {
+    int row;
+    int64_t e0, e1;        // its entries
+    int64_t first;         // the row's first entry
+};
+__device__ inline Piece piece_of(const int64_t *__restrict__ indptr, int id, int split)
+{
+    Piece P;
+    P.row = split > 1 ? id / split : id;
+    P.first = P.e0 = indptr[P.row];
+    P.e1 = indptr[P.row + 1];
+    if (split > 1) {
+        const int64_t len = P.e1 - P.first, k = id - P.row * split;
+        P.e0 = P.first + len * k / split;
+        P.e1 = P.first + len * (k + 1) / split;
+    }
+    return P;
+}
 
 /* counts[k] += 1 for every key k in [0, n_valid) among the first n keys; other keys are skipped. */
 __global__ __launch_bounds__(kBlock) void k_key_count(const int32_t *__restrict__ keys, int64_t n, int n_valid,
@@ -881,43 +973,46 @@ __global__ __launch_bounds__(kBlock) void k_key_count(const int32_t *__restrict_
     }
 }
 
-/* Per row (one wave, kRowChunks chunks of 64 entries loaded together): the
- * number of runs (run_cnt[j]), and the unsorted flag when the row's columns do
- * not ascend strictly. */
+/* Per piece (one wave, kRowChunks chunks of 64 entries loaded together): the number of runs
+ * (run_cnt[id]), and the unsorted flag when the row's columns do not ascend strictly. */
 __global__ __launch_bounds__(kBlock) void k_run_count(const int64_t *__restrict__ indptr,
                                                       const int32_t *__restrict__ indices, int n_rows, int n_voxels,
-                                                      uint32_t *__restrict__ run_cnt, Flags *__restrict__ fl)
+                                                      int split, uint32_t *__restrict__ run_cnt, Flags *__restrict__ fl)
 {
-    const int j = blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);
-    if (j >= n_rows) return;
+    const int id = blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);
+    if (id >= n_rows * split) return;
     const int lane = lane_id();
-    const int64_t e0 = indptr[j], e1 = indptr[j + 1];
+    const Piece P = piece_of(indptr, id, split);
     uint32_t runs = 0;
-    int prev_col = 0, prev_k = -1;                     // entry before the chunk (key -1: none)
-    bool down = false;
-    for (int64_t c = e0; c < e1; c += kRowChunks * kWave) {
+    // the entry before: of the row for the order, of the block for the runs
+    bool down = false, any = P.e0 > P.first;
+    int prev_col = any && P.e0 < P.e1 ? indices[P.e0 - 1] : 0, prev_k = -1;
+    for (int64_t c = P.e0; c < P.e1; c += kRowChunks * kWave) {
         int cols[kRowChunks];
 #pragma unroll
         for (int u = 0; u < kRowChunks; ++u) {
             const int64_t e = c + u * kWave + lane;
-            cols[u] = e < e1 ? indices[e] : 0;
+            cols[u] = e < P.e1 ? indices[e] : 0;
         }
+        if (((c - P.e0) & (kRunBlock - 1)) == 0) prev_k = -1;
 #pragma unroll
         for (int u = 0; u < kRowChunks; ++u) {
             const int64_t e = c + u * kWave + lane;
-            const bool in = e < e1;
+            const bool in = e < P.e1;
             const int col = cols[u];
             const int k = in ? run_key(col, n_voxels) : -3;
             const int cp = from_lane_below(col, prev_col), kp = from_lane_below(k, prev_k);
             runs += (uint32_t)__popcll(__ballot(in && k != kp));
-            down = down || (in && kp != -1 && col <= cp);
+            down = down || (in && (any || lane > 0) && col <= cp);
+            any = true;
             prev_col = __builtin_amdgcn_readlane(col, kWave - 1);
             prev_k = __builtin_amdgcn_readlane(k, kWave - 1);
         }
     }
-    if (lane == 0) run_cnt[j] = runs;
+    if (lane == 0) run_cnt[id] = runs;
     if (__ballot(down) && lane == 0) fl->unsorted = 1;
 }
+static_assert(kRunBlock % (kRowChunks * kWave) == 0, "blocks end with a group of chunks");
 
 /* The path flags (one thread): a run path when the runs are at most half the
  * entries, with masks when the rows ascend; else the radix sort of the entries. */
@@ -937,113 +1032,93 @@ __global__ void k_run_sizes(const int64_t *__restrict__ n_runs, int64_t nnz, Fla
  * invalid run takes the bucket of its column clamped into the grid), row
  * (flagged when invalid), first entry, and an auxiliary word: with ascending
  * rows the mask of its columns (OR of 1 << (col mod 32) over its entries, 0 for
- * an invalid run), else its length (0 for an invalid run).  A lane's run
- * starts at the highest start lane at or below it, or in an earlier chunk
- * (carried); when the columns from that start to the lane are consecutive, as
- * they are on a VOI row without holes, the lane's partial mask is a range of
- * bits, else a segmented OR over the lanes gives it.
+ * an invalid run), else its length (0 for an invalid run).
+ *
+ * A wave stages a block of columns in LDS and lists where its runs start (one
+ * compare, ballot and compaction per 64 entries); then lane i makes the record
+ * of run i from its first and last column: a range of bits when it has no
+ * hole, as on a VOI row, else the OR over its entries.  (A record made at the
+ * lane of its run's last entry took the whole wave through the search for the
+ * run's start: 1.46 ms for 6.5e8 entries against 0.69, 4.8 TB/s.)
  */
 __global__ __launch_bounds__(kBlock) void k_run_emit(const int64_t *__restrict__ indptr,
                                                      const int32_t *__restrict__ indices, int n_rows, int n_voxels,
-                                                     const int64_t *__restrict__ run_ptr, const Flags *__restrict__ fl,
-                                                     uint32_t *__restrict__ run_key_out, int32_t *__restrict__ run_row,
-                                                     float *__restrict__ run_src, uint32_t *__restrict__ run_aux,
-                                                     Gate g)
+                                                     int split, const int64_t *__restrict__ run_ptr,
+                                                     const Flags *__restrict__ fl, Run *__restrict__ out, Gate g)
 {
     if (gate_closed(g)) return;
-    const int j = blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);
-    if (j >= n_rows) return;
+    __shared__ int32_t s_col[kWavesPerBlock][kRunBlock];
+    __shared__ uint16_t s_start[kWavesPerBlock][kRunBlock];
+    const int wave = threadIdx.x >> 6, id = blockIdx.x * kWavesPerBlock + wave;
+    if (id >= n_rows * split) return;   // no barrier below: each wave has its own LDS
     const bool masks = fl->unsorted == 0;
     const int lane = lane_id();
-    const uint64_t upto_lane = lane == kWave - 1 ? ~0ull : ((2ull << lane) - 1ull);   // lanes <= this one
-    const int64_t e0 = indptr[j], e1 = indptr[j + 1];
-    uint32_t r = (uint32_t)run_ptr[j];
-    int prev_k = -1;                                   // run key of the entry before the chunk
-    int open_first = 0;                                // run open at the chunk start: its first column,
-    uint32_t open_len = 0, open_mask = 0;              // its entries and mask so far
-    for (int64_t c = e0; c < e1; c += kRowChunks * kWave) {
-        int cols[kRowChunks];
+    const Piece P = piece_of(indptr, id, split);
+    int32_t *col = s_col[wave];
+    uint16_t *start = s_start[wave];
+    int64_t r = run_ptr[id];
+    for (int64_t c = P.e0; c < P.e1; c += kRunBlock) {
+        const int n = (int)min((int64_t)kRunBlock, P.e1 - c);
+        int cols[kRunSteps];
 #pragma unroll
-        for (int u = 0; u < kRowChunks; ++u) {
-            const int64_t e = c + u * kWave + lane;
-            cols[u] = e < e1 ? indices[e] : 0;
+        for (int u = 0; u < kRunSteps; ++u) {
+            const int x = u * kWave + lane;
+            cols[u] = x < n ? __builtin_nontemporal_load(indices + c + x) : 0;
         }
-        const int64_t en = c + kRowChunks * kWave;     // first entry after this group (uniform address)
-        const int after = en < e1 ? indices[en] : 0;
+        int prev_k = -1, runs = 0;
 #pragma unroll
-        for (int u = 0; u < kRowChunks; ++u) {
-            const int64_t e = c + u * kWave + lane;
-            const bool in = e < e1;
-            const int col = cols[u];
-            const int k = in ? run_key(col, n_voxels) : -3;
+        for (int u = 0; u < kRunSteps; ++u) {
+            if (u * kWave >= n) break;
+            const int x = u * kWave + lane;
+            const int k = x < n ? run_key(cols[u], n_voxels) : -3;
             const int kp = from_lane_below(k, prev_k);
-            // key of the entry after lane 63 (the next chunk's first, or none at the row's end)
-            const int64_t e_next = c + (u + 1) * kWave;
-            const int nx = u + 1 < kRowChunks ? __builtin_amdgcn_readlane(cols[u + 1 < kRowChunks ? u + 1 : u], 0) : after;
-            const int kn = from_lane_above(k, e_next < e1 ? run_key(nx, n_voxels) : -3);
-            const bool start = in && k != kp;
-            const bool end = in && kn != k;
-            const uint64_t m = __ballot(start);
-            const uint64_t upto = m & upto_lane;
-            const int sl = upto ? kWave - 1 - (int)__builtin_clzll(upto) : -1;   // start lane of this lane's run
-            const int fc_here = __shfl(col, sl < 0 ? 0 : sl, kWave);
-            const int fc = sl >= 0 ? fc_here : open_first;
-            const uint32_t len = sl >= 0 ? (uint32_t)(lane - sl + 1) : open_len + (uint32_t)lane + 1u;
-            uint32_t x = 0u;
-            if (masks) {
-                const bool valid = in && k >= 0;
-                const bool ok = !valid || col - fc + 1 == (int)len;
-                if (__ballot(!ok) == 0) {
-                    // columns fc .. col of the bucket
-                    const uint32_t hi = (2u << (col & (kBucketCols - 1))) - 1u;
-                    const uint32_t lo = (1u << (fc & (kBucketCols - 1))) - 1u;
-                    x = valid ? (hi & ~lo) : 0u;
+            prev_k = __builtin_amdgcn_readlane(k, kWave - 1);
+            const uint64_t m = __ballot(x < n && k != kp);
+            if (x < n && k != kp) start[runs + mbcnt64(m)] = (uint16_t)x;
+            runs += __popcll(m);
+            col[x] = cols[u];
+        }
+        wave_lds_fence();
+        for (int i = lane; i < runs; i += kWave) {
+            const int a = start[i], b = i + 1 < runs ? start[i + 1] : n, first = col[a], last = col[b - 1];
+            const bool valid = (uint32_t)first < (uint32_t)n_voxels;
+            uint32_t x = valid ? (uint32_t)(b - a) : 0u;
+            if (masks && valid) {
+                if (last - first == b - a - 1) {
+                    const uint32_t hi = (2u << (last & (kBucketCols - 1))) - 1u;
+                    x = hi & ~((1u << (first & (kBucketCols - 1))) - 1u);
                 } else {
-                    // segmented inclusive OR over the lanes, segments opened by run starts
-                    x = valid ? 1u << (col & (kBucketCols - 1)) : 0u;
-                    int f = start ? 1 : 0;
-#pragma unroll
-                    for (int d = 1; d < kWave; d <<= 1) {
-                        const uint32_t y = __shfl_up(x, d, kWave);
-                        const int fy = __shfl_up(f, d, kWave);
-                        if (lane >= d && !f) {
-                            x |= y;
-                            f = fy;
-                        }
-                    }
-                    if (!f) x |= open_mask;            // no start at or below this lane: the open run
+                    x = 0u;
+                    for (int y = a; y < b; ++y) x |= 1u << (col[y] & (kBucketCols - 1));
                 }
             }
-            const uint32_t id = r + (uint32_t)mbcnt64(m) + (start ? 1u : 0u) - 1u;
-            if (start) {
-                const int clamped = col < 0 ? 0 : (col >= n_voxels ? n_voxels - 1 : col);
-                run_key_out[id] = (uint32_t)(clamped >> kBucketShift);
-                run_row[id] = k >= 0 ? j : (int32_t)((uint32_t)j | kRunFlag);
-                run_src[id] = __uint_as_float((uint32_t)e);
-            }
-            if (end) run_aux[id] = masks ? x : (k >= 0 ? len : 0u);
-            open_first = __builtin_amdgcn_readlane(fc, kWave - 1);
-            open_len = (uint32_t)__builtin_amdgcn_readlane((int)len, kWave - 1);
-            open_mask = (uint32_t)__builtin_amdgcn_readlane((int)x, kWave - 1);
-            r += (uint32_t)__popcll(m);
-            prev_k = __builtin_amdgcn_readlane(k, kWave - 1);
+            const int clamped = first < 0 ? 0 : (first >= n_voxels ? n_voxels - 1 : first);
+            out[r + i] = make_uint4((uint32_t)(clamped >> kBucketShift), (uint32_t)P.row | (valid ? 0u : kRunFlag),
+                                    (uint32_t)(c + a), x);
         }
+        wave_lds_fence();
+        r += runs;
     }
 }
 
-/* Bucket pointers from the sorted bucket keys: b_ptr[b] = first run of bucket b
- * (b_ptr[n_buckets] = R).  Keys ascend, so each b is written once. */
-__global__ __launch_bounds__(kBlock) void k_bucket_bounds(const uint32_t *__restrict__ keys, Count n_runs,
-                                                          int n_buckets, int64_t *__restrict__ b_ptr, Gate g)
+/* Bucket pointers from the runs sorted by bucket: b_ptr[b] = first run of bucket b or above
+ * (b_ptr[n_buckets] = R), by bisection, one thread per bucket.  (Written run by run, each thread
+ * filling the gap before its run's bucket, one thread filled all of an empty stretch of the grid:
+ * 0.24 ms for 3.7e7 runs in 65,536 buckets against 0.02, and 1.1 ms where a few beamlets leave most
+ * of 1e5 buckets empty.) */
+__global__ __launch_bounds__(kBlock) void k_bucket_bounds(const Run *__restrict__ runs, Count n_runs, int n_buckets,
+                                                          int64_t *__restrict__ b_ptr, Gate g)
 {
     if (gate_closed(g)) return;
-    const int64_t R = count_of(n_runs);
-    const int64_t stride = (int64_t)gridDim.x * kBlock;
-    for (int64_t q = (int64_t)blockIdx.x * kBlock + threadIdx.x; q <= R; q += stride) {
-        const int64_t kq = q < R ? (int64_t)keys[q] : n_buckets;
-        const int64_t kp = q > 0 ? (int64_t)keys[q - 1] : -1;
-        for (int64_t b = kp + 1; b <= kq; ++b) b_ptr[b] = q;
+    const int b = blockIdx.x * kBlock + threadIdx.x;
+    if (b > n_buckets) return;
+    int64_t lo = 0, hi = count_of(n_runs);
+    while (lo < hi) {
+        const int64_t mid = lo + ((hi - lo) >> 1);
+        if (runs[mid].x < (uint32_t)b) lo = mid + 1;
+        else hi = mid;
     }
+    b_ptr[b] = lo;
 }
 
 /* Bucket handled by workgroup blockIdx.x: groups of kXcdGroup consecutive
@@ -1063,150 +1138,126 @@ static unsigned xcd_grid(int n_buckets)
     return (unsigned)(((n_buckets + per - 1) / per) * per);
 }
 
-constexpr int kPlaceCap = 1024;     // entries of one batch staged in LDS
-constexpr int kStageUnroll = 8;     // staging chunks whose loads are in flight together
+/* Entries per column (counts[]) from the masks of ascending rows' runs: one wave per bucket, a
+ * popcount of a ballot per column and 64 runs. */
+__global__ __launch_bounds__(kWave) void k_bucket_count(const int64_t *__restrict__ b_ptr,
+                                                        const Run *__restrict__ runs, int n_voxels,
+                                                        int n_buckets, uint32_t *__restrict__ counts, Gate g)
+{
+    if (gate_closed(g)) return;
+    const int b = blockIdx.x, lane = lane_id();
+    const int64_t q0 = b_ptr[b], q1 = b_ptr[b + 1];
+    uint32_t n[kBucketCols] = {};
+    uint32_t next = q0 + lane < q1 ? runs[q0 + lane].w : 0u;
+    for (int64_t q = q0; q < q1; q += kWave) {
+        const uint32_t mask = next;
+        next = q + kWave + lane < q1 ? runs[q + kWave + lane].w : 0u;
+#pragma unroll
+        for (int c = 0; c < kBucketCols; ++c) n[c] += (uint32_t)__popcll(__ballot((mask >> c) & 1u));
+    }
+    uint32_t mine = 0u;
+#pragma unroll
+    for (int c = 0; c < kBucketCols; ++c) mine = lane == c ? n[c] : mine;
+    const int col = (b << kBucketShift) + lane;
+    if (lane < kBucketCols && col < n_voxels) counts[col] = mine;
+}
+
+typedef float vf4u __attribute__((ext_vector_type(4), aligned(4)));
 
 /*
- * Placement for rows with ascending columns, one wave per bucket.
+ * Placement for rows with ascending columns, one workgroup per bucket, 64 runs
+ * per wave at a time (lane = run, in row order over the waves).  A lane takes
+ * its run's values into registers by column: where no run of the wave has a
+ * hole, the value of column c lies (c - first column) entries after the run's
+ * first, so that 16-byte loads of four columns bring each to its own register;
+ * otherwise the run's entries are loaded one by one.  Then for each column the
+ * ballot of the runs that hold it ranks them, and their row ids and values go
+ * out as one contiguous store each, after those of the waves before: neither
+ * entries in LDS nor a search for an entry's column.
  *
- * First the bucket's entries per column: popcounts of ballots over the run
- * masks; their prefix from the bucket's first entry (the exclusive sum of the
- * lengths of all earlier runs) gives the voxel-row pointers of its columns.
- * Then batches of runs (in row order, at most kPlaceCap entries): for column c,
- * the ballot of the runs holding c ranks them, so the entry of run r in column
- * c goes to position (entries of the batch in columns below c) + (runs below r
- * holding c) of the batch's LDS image, which lists the batch's entries column
- * by column.  The image is then written out: each column's part is contiguous
- * after the entries of that column from earlier batches.
+ * Bound by memory, and by how much of the output is open at a time: a column's
+ * cache lines are written piece by piece and leave L2 half filled if too many
+ * buckets are under way.  6.5e8 entries in 3.03 ms (6.9 GB fetched, since runs of
+ * 18 entries share their lines with neighbours, and 6.2 written, 4.3 TB/s)
+ * against 3.97 with each batch's entries reordered in LDS.
  */
-__global__ __launch_bounds__(kWave) void k_place_sorted(
+template <int W>
+__global__ __launch_bounds__(W * kWave) void k_place_sorted(
     const float *__restrict__ values, int n_voxels, int n_buckets, const int64_t *__restrict__ b_ptr,
-    const int32_t *__restrict__ b_rows, const float *__restrict__ b_src, const uint32_t *__restrict__ b_mask,
-    const uint32_t *__restrict__ b_off, const Flags *__restrict__ fl, int64_t *__restrict__ t_indptr, uint32_t nnz,
-    int32_t *__restrict__ t_indices, float *__restrict__ t_values, Gate g)
+    const Run *__restrict__ runs, const int64_t *__restrict__ t_indptr, uint32_t nnz, int32_t *__restrict__ t_indices,
+    float *__restrict__ t_values, Gate g)
 {
     if (gate_closed(g)) return;
     const int b = xcd_bucket();
     if (b >= n_buckets) return;
-    __shared__ uint16_t s_ent[kPlaceCap];        // batch entry p: (run lane << 5) | column
-    __shared__ int32_t s_orow[kPlaceCap];        // LDS image, column by column
-    __shared__ float s_oval[kPlaceCap];
-    __shared__ uint8_t s_ocol[kPlaceCap];
-    __shared__ uint64_t s_cm[kBucketCols];       // runs of the batch holding column c
-    __shared__ uint32_t s_cst[kBucketCols];      // first image position of column c
-    __shared__ uint32_t s_pos[kBucketCols];      // next output position of column c
-    const int lane = lane_id();
-    const int64_t q0 = b_ptr[b], q1 = b_ptr[b + 1], R = b_ptr[n_buckets];
-    const uint32_t total = (uint32_t)fl->total;
-    const uint32_t base = q0 < R ? b_off[q0] : total;
+    __shared__ uint32_t s_n[2][W][kBucketCols];   // entries per column of each wave's batch
+    const int lane = lane_id(), wave = threadIdx.x >> 6;
+    const int64_t q0 = b_ptr[b], q1 = b_ptr[b + 1];
+    // lane c: next output position of column c
+    const int mine = (b << kBucketShift) + lane;
+    uint32_t pos = lane < kBucketCols && mine < n_voxels ? (uint32_t)t_indptr[mine] : 0u;
 
-    // entries per column of the bucket (lane c), the voxel-row pointers
-    uint32_t acc = 0;
-    for (int64_t qb = q0; qb < q1; qb += kWave) {
-        const uint32_t mask = qb + lane < q1 ? b_mask[qb + lane] : 0u;
+    constexpr int kBatch = W * kWave;
+    int64_t q = q0 + threadIdx.x;
+    Run next = q < q1 ? runs[q] : make_uint4(0u, 0u, 0u, 0u);
+    int turn = 0;
+    for (int64_t qb = q0; qb < q1; qb += kBatch, turn ^= 1) {
+        const uint32_t mask = next.w, src = next.z;   // mask 0: an invalid run, not placed
+        const int row = (int)next.y;
+        q += kBatch;
+        next = q < q1 ? runs[q] : make_uint4(0u, 0u, 0u, 0u);
+        const uint32_t lo = mask ? (uint32_t)__builtin_ctz(mask) : 0u, hi = mask ? 31u - (uint32_t)__builtin_clz(mask) : 0u;
+        const uint32_t run = mask >> lo;
+        // whole quads of four columns lie inside the array
+        const bool plain = (run & (run + 1u)) == 0u && src >= (lo & 3u) && (uint64_t)src + ((hi | 3u) - lo) < nnz;
+        float v[kBucketCols];
+        if (__ballot(mask != 0u && !plain) == 0) {
+            const float *p = values + ((int64_t)src - lo);
+#pragma unroll
+            for (int m = 0; m < kBucketCols / 4; ++m) {
+                vf4u x = {0.0f, 0.0f, 0.0f, 0.0f};
+                if ((mask >> (4 * m)) & 15u) x = *reinterpret_cast<const vf4u *>(p + 4 * m);
+                v[4 * m] = x.x;
+                v[4 * m + 1] = x.y;
+                v[4 * m + 2] = x.z;
+                v[4 * m + 3] = x.w;
+            }
+        } else {
+            int64_t e = src;
+#pragma unroll
+            for (int c = 0; c < kBucketCols; ++c) {
+                v[c] = 0.0f;
+                if ((mask >> c) & 1u) v[c] = values[e++];
+            }
+        }
+        // this wave's entries per column, those of the waves before it, of all
+        uint32_t n = 0u;
 #pragma unroll
         for (int c = 0; c < kBucketCols; ++c) {
-            const uint32_t n = (uint32_t)__popcll(__ballot((mask >> c) & 1u));
-            acc += lane == c ? n : 0u;
+            const uint32_t k = (uint32_t)__popcll(__ballot((mask >> c) & 1u));
+            n = lane == c ? k : n;
         }
-    }
-    uint32_t incl = wave_incl_scan(acc);
-    if (lane < kBucketCols) {
-        const uint32_t pos = base + incl - acc;
-        s_pos[lane] = pos;
-        const int col = (b << kBucketShift) + lane;
-        if (col < n_voxels) t_indptr[col] = pos;
-    }
-    if (b == n_buckets - 1 && lane == 0) t_indptr[n_voxels] = total;
-    __builtin_amdgcn_wave_barrier();
-
-    for (int64_t qb = q0; qb < q1;) {
-        const int64_t q = qb + lane;
-        const bool have = q < q1;
-        const int row = have ? (int)((uint32_t)b_rows[q] & ~kRunFlag) : 0;
-        const uint32_t src = have ? __float_as_uint(b_src[q]) : 0u;
-        uint32_t mask = have ? b_mask[q] : 0u;   // 0 for an invalid run
-        uint32_t len = (uint32_t)__popc(mask);
-        uint32_t end = wave_incl_scan(len);
-        // the batch: the leading runs whose entries fit (at least one: a run holds <= 32)
-        const bool fit = have && end <= (uint32_t)kPlaceCap;
-        const int take = __popcll(__ballot(fit));
-        const uint32_t T = (uint32_t)__shfl(end, take - 1, kWave);
-        if (!fit) {
-            mask = 0u;
-            len = 0u;
+        if (lane < kBucketCols) s_n[turn][wave][lane] = n;
+        __syncthreads();   // the buffers alternate: one barrier a batch
+        uint32_t at = pos;
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+            const uint32_t k = s_n[turn][w][lane & (kBucketCols - 1)];
+            at += w < wave ? k : 0u;
+            pos += k;
         }
-        const uint32_t excl = end - len;
-        // runs of the batch per column, and the columns' first image positions
-        uint64_t cm = 0;
 #pragma unroll
         for (int c = 0; c < kBucketCols; ++c) {
-            const uint64_t m = __ballot((mask >> c) & 1u);
-            cm = lane == c ? m : cm;
-        }
-        const uint32_t cnt = (uint32_t)__popcll(cm);
-        uint32_t cinc = wave_incl_scan(cnt);
-        const uint32_t cst = cinc - cnt;
-        if (lane < kBucketCols) {
-            s_cm[lane] = cm;
-            s_cst[lane] = cst;
-        }
-        // batch entries in run order: entry excl + i of run `lane` is its mask's i-th column
-        {
-            uint32_t x = mask, p = excl;
-            while (__ballot(x != 0u)) {
-                if (x != 0u) {
-                    const uint32_t c = (uint32_t)__builtin_ctz(x);
-                    x &= x - 1u;
-                    s_ent[p] = (uint16_t)(((uint32_t)lane << kBucketShift) | c);
-                    ++p;
-                }
+            const bool in = (mask >> c) & 1u;
+            const uint64_t m = __ballot(in);
+            const uint32_t p = (uint32_t)__builtin_amdgcn_readlane((int)at, c);
+            // the bound always holds for consistent runs; it keeps every store inside the arrays
+            if (in && p + (uint32_t)__popcll(m) <= nnz) {
+                const int rank = mbcnt64(m);
+                (t_indices + p)[rank] = row;
+                (t_values + p)[rank] = v[c];
             }
         }
-        __builtin_amdgcn_wave_barrier();
-        // stage the values into the image, kStageUnroll chunks of loads at a time
-        for (uint32_t g0 = 0; g0 < T; g0 += kStageUnroll * kWave) {
-            uint32_t ent[kStageUnroll];
-            float v[kStageUnroll];
-#pragma unroll
-            for (int u = 0; u < kStageUnroll; ++u) {
-                const uint32_t p = g0 + u * kWave + lane;
-                const bool in = p < T;
-                ent[u] = in ? (uint32_t)s_ent[p] : 0u;
-                const int rr = (int)(ent[u] >> kBucketShift);
-                // shuffles on every lane; loads only for entries of the batch
-                const uint32_t e = __shfl(src, rr, kWave) + (p - __shfl(excl, rr, kWave));
-                v[u] = in ? values[e] : 0.0f;
-            }
-#pragma unroll
-            for (int u = 0; u < kStageUnroll; ++u) {
-                const uint32_t p = g0 + u * kWave + lane;
-                const int rr = (int)(ent[u] >> kBucketShift);
-                const int c = (int)(ent[u] & (kBucketCols - 1));
-                const int rowr = __shfl(row, rr, kWave);
-                if (p < T) {
-                    const uint64_t below = (1ull << rr) - 1ull;
-                    const uint32_t d = s_cst[c] + (uint32_t)__popcll(s_cm[c] & below);
-                    s_orow[d] = rowr;
-                    s_oval[d] = v[u];
-                    s_ocol[d] = (uint8_t)c;
-                }
-            }
-        }
-        __builtin_amdgcn_wave_barrier();
-        // write the image out
-        for (uint32_t i = lane; i < T; i += kWave) {
-            const int c = s_ocol[i];
-            const uint32_t gp = s_pos[c] + (i - s_cst[c]);
-            if (gp < nnz) {   // always true for consistent runs; keeps every store in bounds
-                t_indices[gp] = s_orow[i];
-                t_values[gp] = s_oval[i];
-            }
-        }
-        __builtin_amdgcn_wave_barrier();
-        if (lane < kBucketCols) s_pos[lane] += cnt;
-        __builtin_amdgcn_wave_barrier();
-        qb += take;
     }
 }
 
@@ -1217,16 +1268,16 @@ struct RunBatch {
     uint32_t src, len, excl, total;
 };
 
-__device__ inline RunBatch load_runs(int64_t qb, int64_t q1, const int32_t *__restrict__ b_rows,
-                                     const float *__restrict__ b_src, const uint32_t *__restrict__ b_len)
+__device__ inline RunBatch load_runs(int64_t qb, int64_t q1, const Run *__restrict__ runs)
 {
     const int lane = lane_id();
     const int64_t q = qb + lane;
     RunBatch B{0, 0u, 0u, 0u, 0u};
     if (q < q1) {
-        B.row = (int)((uint32_t)b_rows[q] & ~kRunFlag);
-        B.src = __float_as_uint(b_src[q]);
-        B.len = b_len[q];   // 0 for an invalid run
+        const Run r = runs[q];
+        B.row = (int)(r.y & ~kRunFlag);
+        B.src = r.z;
+        B.len = r.w;   // 0 for an invalid run
     }
     uint32_t incl = wave_incl_scan(B.len);
     B.excl = incl - B.len;
@@ -1258,8 +1309,7 @@ __device__ inline int run_of(const RunBatch &B, uint32_t c0, int &rcur)
  */
 __global__ __launch_bounds__(kWave) void k_place_any(
     const int32_t *__restrict__ indices, const float *__restrict__ values, int n_voxels, int n_buckets,
-    const int64_t *__restrict__ b_ptr, const int32_t *__restrict__ b_rows, const float *__restrict__ b_src,
-    const uint32_t *__restrict__ b_len, const int64_t *__restrict__ t_indptr, uint32_t nnz,
+    const int64_t *__restrict__ b_ptr, const Run *__restrict__ runs, const int64_t *__restrict__ t_indptr, uint32_t nnz,
     int32_t *__restrict__ t_indices, float *__restrict__ t_values, Gate g)
 {
     if (gate_closed(g)) return;
@@ -1277,7 +1327,7 @@ __global__ __launch_bounds__(kWave) void k_place_any(
     const int64_t q0 = b_ptr[b], q1 = b_ptr[b + 1];
     const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (kWave - lane));   // lanes under this one
     for (int64_t qb = q0; qb < q1; qb += kWave) {
-        const RunBatch B = load_runs(qb, q1, b_rows, b_src, b_len);
+        const RunBatch B = load_runs(qb, q1, runs);
         int rcur = 0;
         for (uint32_t c0 = 0; c0 < B.total; c0 += kWave) {
             const uint32_t p = c0 + lane;
@@ -1313,8 +1363,19 @@ __global__ __launch_bounds__(kWave) void k_place_any(
 
 /* Workspace layout of the transpose (offsets from a 256-byte aligned base). */
 struct TransposeLayout {
-    size_t key[2], row[2], val[2], hist, offs, partial, counts, bptr, flags, run_cnt, run_ptr, total;
+    size_t key[2], row[2], val[2];   // of the entry path; the run path keeps records in the same space
+    size_t hist, partial, counts, bptr, flags, run_cnt, run_ptr, total;
 };
+
+/* Pieces per row of the run kernels: at least kRunWaves waves in all where the rows are too few, of
+ * no less than 512 entries each (on average), so that the runs that pieces cut stay few.  (32 rows
+ * of 5e5 entries: both run kernels 17 us against 0.9 ms with a wave per row.) */
+constexpr int kRunWaves = 8192;
+static int run_split(int64_t nnz, int n_rows)
+{
+    const int64_t want = (kRunWaves + n_rows - 1) / n_rows, most = nnz / n_rows / 512;
+    return (int)std::max<int64_t>(1, std::min(want, most));
+}
 
 static TransposeLayout transpose_layout(int64_t nnz, int n_voxels, int n_rows)
 {
@@ -1328,21 +1389,21 @@ static TransposeLayout transpose_layout(int64_t nnz, int n_voxels, int n_rows)
     const int64_t n_tiles = (nnz + kSortTile - 1) / kSortTile;
     const int64_t n_hist = (int64_t)kRadix * (n_tiles > 0 ? n_tiles : 1);
     const int64_t nb = (n_voxels + kBucketCols - 1) >> kBucketShift;
-    int64_t n_scan = std::max<int64_t>(std::max<int64_t>(n_hist, n_voxels), std::max<int64_t>(n_rows, (nnz + 1) / 2));
+    int64_t n_scan = std::max<int64_t>(std::max<int64_t>(n_hist, n_voxels), (int64_t)std::max(n_rows, 1) * (n_rows > 0 ? run_split(nnz, n_rows) : 1));
     const size_t e = (size_t)(nnz > 0 ? nnz : 1);
+    const size_t pieces = n_rows > 0 ? (size_t)n_rows * run_split(nnz, n_rows) : 1;
     for (int b = 0; b < 2; ++b) {
         L.key[b] = take(sizeof(uint32_t) * e);
         L.row[b] = take(sizeof(int32_t) * e);
         L.val[b] = take(sizeof(float) * e);
     }
     L.hist = take(sizeof(uint32_t) * (size_t)n_hist);
-    L.offs = take(sizeof(uint32_t) * (size_t)n_hist);
     L.partial = take(sizeof(uint32_t) * (size_t)((n_scan + kScanChunk - 1) / kScanChunk + 1));
     L.counts = take(sizeof(uint32_t) * ((size_t)n_voxels + 1));
     L.bptr = take(sizeof(int64_t) * (size_t)(nb + 1));
     L.flags = take(sizeof(Flags));
-    L.run_cnt = take(sizeof(uint32_t) * (size_t)(n_rows > 0 ? n_rows : 1));
-    L.run_ptr = take(sizeof(int64_t) * ((size_t)n_rows + 1));
+    L.run_cnt = take(sizeof(uint32_t) * pieces);
+    L.run_ptr = take(sizeof(int64_t) * (pieces + 1));
     L.total = off;
     return L;
 }
@@ -1366,77 +1427,84 @@ static unsigned stride_grid(int64_t items)
     return (unsigned)std::max<int64_t>(1, std::min<int64_t>(items, 4096));
 }
 
-/* Exclusive (inclusive with INCL) scan of n uint32 values in -> out (OUT =
- * uint32_t or int64_t; out may be in); n is a host count or, with n.dev, a
- * device count at most n_max.  partial[nblocks] receives the total, and
- * *total64 too when given. */
-template <typename OUT, bool INCL = false, bool POPC = false>
+/* Exclusive scan of n uint32 values in -> out (OUT = uint32_t or int64_t; out may be in); n is a
+ * host count or, with n.dev, a device count at most n_max.  partial[nblocks] receives the total,
+ * and *total64 too when given. */
+template <typename OUT>
 static hipError_t scan_excl(const uint32_t *in, Count n, int64_t n_max, uint32_t *partial, OUT *out,
                             int64_t *total64, Gate g, hipStream_t s)
 {
     const unsigned nb = stride_grid((n_max + kScanChunk - 1) / kScanChunk);
-    hipLaunchKernelGGL(k_scan_reduce<POPC>, dim3(nb), dim3(kBlock), 0, s, in, n, partial, g);
+    hipLaunchKernelGGL(k_scan_reduce, dim3(nb), dim3(kBlock), 0, s, in, n, partial, g);
     hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(kScanTop), 0, s, partial, n, total64, g);
-    hipLaunchKernelGGL((k_scan_down<OUT, INCL, POPC>), dim3(nb), dim3(kBlock), 0, s, in, n, partial, out, g);
+    hipLaunchKernelGGL(k_scan_down<OUT>, dim3(nb), dim3(kBlock), 0, s, in, n, partial, out, g);
     return hipGetLastError();
 }
-
-/* Optional fourth payload of a radix sort: input, ping-pong buffers, output. */
-struct Extra {
-    const uint32_t *in;
-    uint32_t *b0, *b1, *out;
-};
 
 /*
  * One stable LSD radix sort of (key, row, value) triples by key: `passes`
  * passes of 8 bits, keys above clamp sorted as clamp, ping-pong through
  * (k1, r1, v1) and (k0, r0, v0) (the input may be separate), the last pass
- * writing rows and values to (rows_out, vals_out), and with keys_out its keys
- * to the pass's own key buffer (*keys_out = that buffer); with x.in a fourth
- * payload rides along (through x.b1, x.b0, to x.out).  n is a host or device
- * count, at most n_max.
+ * writing rows and values to (rows_out, vals_out).
  */
-static hipError_t radix_sort(const uint32_t *keys, const int32_t *rows, const float *vals, Count n, int64_t n_max,
-                             uint32_t clamp, int passes, uint32_t *k0, int32_t *r0, float *v0, uint32_t *k1,
-                             int32_t *r1, float *v1, int32_t *rows_out, float *vals_out, uint32_t **keys_out,
-                             Extra x, uint32_t *hist, uint32_t *offs, uint32_t *partial, int64_t *hist_len_dev, Gate g,
-                             hipStream_t s)
+static hipError_t sort_entries(const uint32_t *keys, const int32_t *rows, const float *vals, int64_t n, uint32_t clamp,
+                               int passes, uint32_t *k0, int32_t *r0, float *v0, uint32_t *k1, int32_t *r1, float *v1,
+                               int32_t *rows_out, float *vals_out, uint32_t *hist, uint32_t *partial, Gate g,
+                               hipStream_t s)
 {
-    const int64_t tiles_max = (n_max + kSortTile - 1) / kSortTile;
-    const unsigned grid = stride_grid(tiles_max);
-    const Count hn = hist_len_dev ? Count{0, hist_len_dev} : Count{(int64_t)kRadix * tiles_max, nullptr};
-    const uint32_t *kin = keys;
-    const int32_t *rin = rows;
-    const float *vin = vals;
-    const uint32_t *xin = x.in;
+    const int64_t tiles = (n + kSortTile - 1) / kSortTile, n_hist = (int64_t)kRadix * tiles;
+    const unsigned grid = stride_grid(tiles);
+    const Count cn{n, nullptr};
     hipError_t e;
     for (int p = 0; p < passes; ++p) {
         const int shift = p * kRadixBits;
-        const bool last = p == passes - 1;
-        uint32_t *kbuf = (p & 1) ? k0 : k1;
-        uint32_t *kout = last ? (keys_out ? kbuf : nullptr) : kbuf;
-        int32_t *rout = last ? rows_out : ((p & 1) ? r0 : r1);
-        float *vout = last ? vals_out : ((p & 1) ? v0 : v1);
-        uint32_t *xout = last ? x.out : ((p & 1) ? x.b0 : x.b1);
-        hipLaunchKernelGGL(k_rs_hist, dim3(grid), dim3(kBlock), 0, s, kin, n, clamp, shift, hist, g);
-        if ((e = scan_excl<uint32_t>(hist, hn, (int64_t)kRadix * tiles_max, partial, offs, nullptr, g, s)) !=
-            hipSuccess)
+        const bool last = p == passes - 1, odd = p & 1;
+        uint32_t *kout = last ? nullptr : (odd ? k0 : k1);
+        int32_t *rout = last ? rows_out : (odd ? r0 : r1);
+        float *vout = last ? vals_out : (odd ? v0 : v1);
+        hipLaunchKernelGGL(k_rs_hist<1>, dim3(grid), dim3(kBlock), 0, s, keys, cn, clamp, shift, hist, g);
+        if ((e = scan_excl<uint32_t>(hist, Count{n_hist, nullptr}, n_hist, partial, hist, nullptr, g, s)) != hipSuccess)
             return e;
-        if (x.in)
-            hipLaunchKernelGGL(k_rs_scatter<true>, dim3(grid), dim3(kBlock), 0, s, kin, rin, vin, xin, n, clamp, shift,
-                               offs, kout, rout, vout, xout, g);
-        else
-            hipLaunchKernelGGL(k_rs_scatter<false>, dim3(grid), dim3(kBlock), 0, s, kin, rin, vin, nullptr, n, clamp,
-                               shift, offs, kout, rout, vout, nullptr, g);
+        hipLaunchKernelGGL(k_rs_scatter, dim3(grid), dim3(kSortBlock), 0, s, keys, rows, vals, cn, clamp, shift, hist,
+                           kout, rout, vout, g);
         if ((e = hipGetLastError()) != hipSuccess) return e;
-        if (last && keys_out) *keys_out = kout;
-        kin = kout;
-        rin = rout;
-        vin = vout;
-        xin = xout;
+        keys = kout;
+        rows = rout;
+        vals = vout;
     }
     return hipSuccess;
 }
+
+/* Stable LSD radix sort of run records by key through b and a; a holds the input, *sorted the
+ * result.  n is a device count, at most n_max. */
+static hipError_t sort_runs(Run *a, Run *b, Count n, int64_t n_max, int passes, uint32_t *hist, uint32_t *partial,
+                            int64_t *hist_len, Gate g, Run **sorted, hipStream_t s)
+{
+    const int64_t tiles_max = (n_max + kSortTile - 1) / kSortTile;
+    const unsigned grid = stride_grid(tiles_max);
+    hipError_t e;
+    for (int p = 0; p < passes; ++p) {
+        const int shift = p * kRadixBits;
+        hipLaunchKernelGGL(k_rs_hist<4>, dim3(grid), dim3(kBlock), 0, s, reinterpret_cast<const uint32_t *>(a), n,
+                           0xffffffffu, shift, hist, g);
+        if ((e = scan_excl<uint32_t>(hist, Count{0, hist_len}, (int64_t)kRadix * tiles_max, partial, hist, nullptr, g,
+                                     s)) != hipSuccess)
+            return e;
+        hipLaunchKernelGGL(k_run_scatter, dim3(grid), dim3(kSortBlock), 0, s, a, n, shift, hist, b, g);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+        std::swap(a, b);
+    }
+    *sorted = a;
+    return hipSuccess;
+}
+
+// Large buckets are placed by four waves, and the LDS reserved keeps the workgroups per CU at
+// three, so that the open cache lines stay in L2 (1e4 entries per bucket: placement 3.03 ms against
+// 3.39 with as many as fit and 3.83 with one wave each; whole transposes of 715 per bucket 0.64 ms
+// against 0.68 with one wave); small ones, whose latency counts, by one wave and as many as fit
+// (290 per bucket 0.33 against 0.38, 160 per bucket 0.23 against 0.34).
+constexpr int64_t kPlaceMany = 512;              // entries per bucket
+constexpr unsigned kPlaceReserve = 45 * 1024;
 
 hipError_t launch_transpose(const int64_t *indptr, const int32_t *indices, const float *values, int n_rows,
                             int n_voxels, int64_t nnz, int64_t *t_indptr, int32_t *t_indices, float *t_values,
@@ -1448,7 +1516,6 @@ hipError_t launch_transpose(const int64_t *indptr, const int32_t *indices, const
     int32_t *row[2] = {reinterpret_cast<int32_t *>(ws + L.row[0]), reinterpret_cast<int32_t *>(ws + L.row[1])};
     float *val[2] = {reinterpret_cast<float *>(ws + L.val[0]), reinterpret_cast<float *>(ws + L.val[1])};
     uint32_t *hist = reinterpret_cast<uint32_t *>(ws + L.hist);
-    uint32_t *offs = reinterpret_cast<uint32_t *>(ws + L.offs);
     uint32_t *partial = reinterpret_cast<uint32_t *>(ws + L.partial);
     uint32_t *counts = reinterpret_cast<uint32_t *>(ws + L.counts);
     Flags *fl = reinterpret_cast<Flags *>(ws + L.flags);
@@ -1457,79 +1524,67 @@ hipError_t launch_transpose(const int64_t *indptr, const int32_t *indices, const
     const Gate always{nullptr, 0};
     hipError_t e;
 
-    if (nnz == 0 || n_rows == 0) {   // empty voxel rows
-        hipLaunchKernelGGL(k_zero_u32, dim3(blocks_of((int64_t)n_voxels + 1, kBlock)), dim3(kBlock), 0, s, counts,
-                           (int64_t)n_voxels + 1);
+    hipLaunchKernelGGL(k_zero_u32, dim3(blocks_of((int64_t)n_voxels + 1, kBlock)), dim3(kBlock), 0, s, counts,
+                       (int64_t)n_voxels + 1);
+    if (nnz == 0 || n_rows == 0)   // empty voxel rows
         return scan_excl<int64_t>(counts, Count{n_voxels, nullptr}, n_voxels, partial, t_indptr, t_indptr + n_voxels,
                                   always, s);
-    }
 
-    // runs of every row and the unsorted flag; run pointers; the path flags
+    // runs of every piece and the unsorted flag; run pointers; the path flags
+    const int split = run_split(nnz, n_rows);
+    const int64_t pieces = (int64_t)n_rows * split;
     hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(kBlock), 0, s, reinterpret_cast<uint32_t *>(fl),
                        (int64_t)(sizeof(Flags) / 4));
-    hipLaunchKernelGGL(k_run_count, dim3(blocks_of(n_rows, kWavesPerBlock)), dim3(kBlock), 0, s, indptr, indices,
-                       n_rows, n_voxels, run_cnt, fl);
-    if ((e = scan_excl<int64_t>(run_cnt, Count{n_rows, nullptr}, n_rows, partial, run_ptr, run_ptr + n_rows, always,
+    hipLaunchKernelGGL(k_run_count, dim3(blocks_of(pieces, kWavesPerBlock)), dim3(kBlock), 0, s, indptr, indices,
+                       n_rows, n_voxels, split, run_cnt, fl);
+    if ((e = scan_excl<int64_t>(run_cnt, Count{pieces, nullptr}, pieces, partial, run_ptr, run_ptr + pieces, always,
                                 s)) != hipSuccess)
         return e;
-    hipLaunchKernelGGL(k_run_sizes, dim3(1), dim3(1), 0, s, run_ptr + n_rows, nnz, fl);
+    const Count n_runs{0, run_ptr + pieces};
+    hipLaunchKernelGGL(k_run_sizes, dim3(1), dim3(1), 0, s, n_runs.dev, nnz, fl);
     const Gate runs{&fl->use_runs, 1}, entries{&fl->use_runs, 0}, counted{&fl->need_counts, 1},
         masked{&fl->sorted, 1}, any{&fl->any, 1};
 
-    // entry path and unsorted rows: entries per column by atomics, the voxel-row pointers
-    hipLaunchKernelGGL(k_zero_u32, dim3(blocks_of((int64_t)n_voxels + 1, kBlock)), dim3(kBlock), 0, s, counts,
-                       (int64_t)n_voxels + 1);
+    // run paths: at most nnz / 2 records of 16 bytes, in the space of key, row and val of each side
+    const int nb = (n_voxels + kBucketCols - 1) >> kBucketShift;
+    const int64_t half = (nnz + 1) / 2;
+    Run *ra = reinterpret_cast<Run *>(key[0]), *rb = reinterpret_cast<Run *>(key[1]), *sorted = nullptr;
+    int64_t *bptr = reinterpret_cast<int64_t *>(ws + L.bptr);
+    hipLaunchKernelGGL(k_run_emit, dim3(blocks_of(pieces, kWavesPerBlock)), dim3(kBlock), 0, s, indptr, indices,
+                       n_rows, n_voxels, split, run_ptr, fl, ra, runs);
+    // stable sort of the runs by bucket
+    if ((e = sort_runs(ra, rb, n_runs, half, transpose_passes(nb), hist, partial, &fl->hist_len, runs, &sorted, s)) !=
+        hipSuccess)
+        return e;
+    hipLaunchKernelGGL(k_bucket_bounds, dim3(blocks_of((int64_t)nb + 1, kBlock)), dim3(kBlock), 0, s, sorted, n_runs,
+                       nb, bptr, runs);
+
+    // entries per column (from the run masks; entry path and unsorted rows: by atomics), the
+    // voxel-row pointers
+    hipLaunchKernelGGL(k_bucket_count, dim3(nb), dim3(kWave), 0, s, bptr, sorted, n_voxels, nb, counts, masked);
     hipLaunchKernelGGL(k_key_count, dim3(stride_grid(blocks_of(nnz, kBlock))), dim3(kBlock), 0, s, indices, nnz,
                        n_voxels, counts, counted);
     if ((e = scan_excl<int64_t>(counts, Count{n_voxels, nullptr}, n_voxels, partial, t_indptr, t_indptr + n_voxels,
-                                counted, s)) != hipSuccess)
+                                always, s)) != hipSuccess)
         return e;
 
-    // run paths: at most nnz / 2 runs.  Run records (bucket, row, first entry, mask or
-    // length) in the first halves of key[0], row[0], val[0] and in key[0] + half; the
-    // sort's other buffers are the first halves of key/row/val[1] and key[1] + half; the
-    // sorted rows, first entries and masks or lengths go to row[0] + half, val[0] + half
-    // and row[1] + half, the entry offsets of the sorted runs to val[1] + half
-    const int nb = (n_voxels + kBucketCols - 1) >> kBucketShift;
-    {
-        const int64_t half = (nnz + 1) / 2;
-        int32_t *brow = row[0] + half;
-        float *bsrc = val[0] + half;
-        uint32_t *baux = reinterpret_cast<uint32_t *>(row[1]) + half;
-        uint32_t *boff = reinterpret_cast<uint32_t *>(val[1]) + half;
-        int64_t *bptr = reinterpret_cast<int64_t *>(ws + L.bptr);
-        const Count n_runs{0, run_ptr + n_rows};
-        hipLaunchKernelGGL(k_run_emit, dim3(blocks_of(n_rows, kWavesPerBlock)), dim3(kBlock), 0, s, indptr, indices,
-                           n_rows, n_voxels, run_ptr, fl, key[0], row[0], val[0], key[0] + half, runs);
-        // stable sort of the runs by bucket
-        uint32_t *skeys = nullptr;
-        const Extra aux{key[0] + half, key[0] + half, key[1] + half, baux};
-        if ((e = radix_sort(key[0], row[0], val[0], n_runs, half, 0xffffffffu, transpose_passes(nb), key[0], row[0],
-                            val[0], key[1], row[1], val[1], brow, bsrc, &skeys, aux, hist, offs, partial,
-                            &fl->hist_len, runs, s)) != hipSuccess)
-            return e;
-        hipLaunchKernelGGL(k_bucket_bounds, dim3(stride_grid(blocks_of(half + 1, kBlock))), dim3(kBlock), 0, s, skeys,
-                           n_runs, nb, bptr, runs);
-        // rows ascending: entry offset of every sorted run, then the placement (and the pointers)
-        if ((e = scan_excl<uint32_t, false, true>(baux, n_runs, half, partial, boff, &fl->total, masked, s)) !=
-            hipSuccess)
-            return e;
-        hipLaunchKernelGGL(k_place_sorted, dim3(xcd_grid(nb)), dim3(kWave), 0, s, values, n_voxels, nb, bptr, brow,
-                           bsrc, baux, boff, fl, t_indptr, (uint32_t)nnz, t_indices, t_values, masked);
-        // rows in any order
-        hipLaunchKernelGGL(k_place_any, dim3(xcd_grid(nb)), dim3(kWave), 0, s, indices, values, n_voxels, nb, bptr,
-                           brow, bsrc, baux, t_indptr, (uint32_t)nnz, t_indices, t_values, any);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-    }
+    if (nnz >= kPlaceMany * nb)
+        hipLaunchKernelGGL(k_place_sorted<4>, dim3(xcd_grid(nb)), dim3(4 * kWave), kPlaceReserve, s, values, n_voxels,
+                           nb, bptr, sorted, t_indptr, (uint32_t)nnz, t_indices, t_values, masked);
+    else
+        hipLaunchKernelGGL(k_place_sorted<1>, dim3(xcd_grid(nb)), dim3(kWave), 0, s, values, n_voxels, nb, bptr,
+                           sorted, t_indptr, (uint32_t)nnz, t_indices, t_values, masked);
+    hipLaunchKernelGGL(k_place_any, dim3(xcd_grid(nb)), dim3(kWave), 0, s, indices, values, n_voxels, nb, bptr, sorted,
+                       t_indptr, (uint32_t)nnz, t_indices, t_values, any);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
 
     // entry path: row id of every entry (into row[0]), then a radix sort of the entries by
     // column (invalid columns as n_voxels, sorted last)
     hipLaunchKernelGGL(k_expand_rows, dim3(blocks_of(n_rows, kWavesPerBlock)), dim3(kBlock), 0, s, indptr, n_rows, nnz,
                        row[0], entries);
-    return radix_sort(reinterpret_cast<const uint32_t *>(indices), row[0], values, Count{nnz, nullptr}, nnz,
-                      (uint32_t)n_voxels, transpose_passes(n_voxels + 1), key[0], row[0], val[0], key[1], row[1],
-                      val[1], t_indices, t_values, nullptr, Extra{nullptr, nullptr, nullptr, nullptr}, hist, offs,
-                      partial, nullptr, entries, s);
+    return sort_entries(reinterpret_cast<const uint32_t *>(indices), row[0], values, nnz, (uint32_t)n_voxels,
+                        transpose_passes(n_voxels + 1), key[0], row[0], val[0], key[1], row[1], val[1], t_indices,
+                        t_values, hist, partial, entries, s);
 }
 
 /*
