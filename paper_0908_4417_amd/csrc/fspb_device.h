@@ -117,7 +117,9 @@ struct alignas(16) PlanDev {
     float d_floor;               // lower bound applied to D: 0 when every weight (c1) and every
                                  // depth-dose (A) entry is >= 0, so that D >= 0 exactly; else -inf
     int32_t erf_square;          // every beam's beamlets are square (a = b)
-    int32_t erf_mode;            // how the fill reads erf (0..3, see erf_mirrored_mode in the kernels)
+    int32_t erf_mode;            // how the fill reads erf (0..4, see erf_mirrored_mode in the kernels)
+    int32_t sig_prop;            // every term's sigma law is a fixed multiple of the first's
+    float pdd_step;              // 1 / pdd_inv_step
 };
 
 /* Caller-owned CSR output of one plan (device pointers). */
@@ -139,11 +141,13 @@ hipError_t launch_scan(const PlanDev *dplan, const OutDev *dout, const PlanDev &
 /* Fill rows row0 .. row0 + n_rows - 1 (dout->row0 must equal row0). */
 hipError_t launch_fill(const PlanDev *dplan, const OutDev *dout, const PlanDev &h, int row0, int n_rows,
                        hipStream_t s);
-/* Dynamic LDS of one fill workgroup: in the form launch_fill uses, or in a given erf table form. */
+/* LDS of one fill workgroup (the erf table and the dynamic part): in the form launch_fill uses, or in
+ * a given erf table form; and the dynamic part alone. */
+size_t fill_dynamic_bytes(const PlanDev &h);
 size_t fill_shared_bytes(const PlanDev &h);
 size_t fill_shared_bytes(const PlanDev &h, bool mirrored_erf);
 bool fill_mirrored_erf(const PlanDev &h);
-/* The erf mode of the plan's fill when it stages the mirrored table (1, 2 or 3). */
+/* The erf mode of the plan's fill when it stages the mirrored table (1 to 4). */
 int mirrored_erf_mode(const PlanDev &h);
 /* 1 when the mirrored erf table keeps the plan's fill at the same workgroups per CU as the
  * compact table (occupancy query for the current device); 0 otherwise. */

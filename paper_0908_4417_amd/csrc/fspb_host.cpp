@@ -419,6 +419,21 @@ const std::vector<float2> &fill_erf_table()
  * the slope being >= 0); for tables, c2 / c3 is a ratio of two linear
  * functions on each depth interval, so its largest value sits on a node.
  */
+/* True when sigma_k(d) / sigma_0(d) is the same at every depth for each term of the analytic form
+ * (to FP64 rounding), and sigma_0 of a size whose product with a distance stays far from FP32's
+ * limits. */
+bool proportional_sigmas(const fspb_kernel *K)
+{
+    if (K->tables) return false;
+    const double a = K->sigma0[0], b = K->sigma_slope[0];
+    if (!(a > 1e-6 && a < 1e6 && b < 1e6)) return false;
+    for (int i = 1; i < K->n_terms; ++i) {
+        const double x = K->sigma_slope[i] * a, y = b * K->sigma0[i];
+        if (std::fabs(x - y) > 1e-12 * std::max(x, y) || !(K->sigma0[i] > 1e-6 && K->sigma0[i] < 1e6)) return false;
+    }
+    return true;
+}
+
 /* True when every weight (c1) and every depth-dose (A) value of the kernel is
  * >= 0: then each coefficient of Eq. 2-3 is >= 0 (each bracket of Eq. 3 is). */
 bool nonnegative_kernel(const fspb_kernel *K)
@@ -590,6 +605,7 @@ fspb_status fspb_plan_create(const fspb_grid *g, const fspb_beam *beams, int32_t
         h.c2[i] = on ? (float)K->width_scale[i] : 1.0f;
     }
     h.pdd_inv_step = (float)(1.0 / K->pdd_step);
+    h.pdd_step = (float)K->pdd_step;
     h.pdd_max = (float)(K->n_pdd - 1);
     if (const fspb_kernel_tables *T = K->tables) {
         h.gen = 1;
@@ -813,6 +829,7 @@ fspb_status fspb_plan_create(const fspb_grid *g, const fspb_beam *beams, int32_t
     int dev = 0;
     FSPB_HIP(hipGetDevice(&dev), "get device");
     h.erf_nc = erf_args_bounded(K, beams, n_beams) ? 1 : 0;
+    h.sig_prop = proportional_sigmas(K) ? 1 : 0;
     h.d_floor = nonnegative_kernel(K) ? 0.0f : -HUGE_VALF;
     h.erf_square = 1;
     for (int32_t b = 0; b < n_beams; ++b)
@@ -1046,7 +1063,7 @@ fspb_status fspb_plan_info(const fspb_plan *p, fspb_plan_desc *d)
     d->n_tiles = p->h.n_tiles;
     d->max_table = p->h.max_table;
     d->fill_lds_bytes = (int32_t)fspb::fill_shared_bytes(p->h);
-    d->fill_erf_mode = p->h.use_mlp ? 0 : p->h.erf_mode;
+    d->fill_erf_mode = p->h.use_mlp ? 0 : std::min(p->h.erf_mode, 3);   // 4 reads erf as 3 does
     return FSPB_OK;
 }
 
@@ -1279,7 +1296,7 @@ fspb_status fspb_batch_create(fspb_plan *const *plans, int32_t n_plans, void *wo
         start[1][i + 1] = start[1][i] + h.n_beamlets;
         start[2][i + 1] = start[2][i] + h.n_beamlets;
         b->max_terms = std::max(b->max_terms, h.n_terms);
-        b->lds = std::max(b->lds, fspb::fill_shared_bytes(h));   // each plan's erf table form
+        b->lds = std::max(b->lds, fspb::fill_dynamic_bytes(h));   // beside an erf table of either form
         b->outs[i].overflow = plans[i]->d_overflow;
     }
     for (int st = 0; st < kWaveStages; ++st) b->total[st] = start[st][n_plans];

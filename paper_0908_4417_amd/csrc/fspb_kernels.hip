@@ -650,9 +650,39 @@ __device__ inline float erf_m_lo(const float2 *__restrict__ tab, float x)
  *      -erf(-z) so that it too can only leave the table below (no clamp at
  *      all, and a saturated bracket is exactly 0); in the analytic form the
  *      first term's weight is folded into the staged depth dose.  Only for
- *      kernels with D >= 0 (non-negative weights and depth dose).
+ *      kernels with D >= 0 (non-negative weights and depth dose);
+ *   4  analytic form only: as 3, with every term's sigma(d) a fixed multiple of
+ *      the first's, so that one reciprocal serves t' and all sigmas.
+ * Modes 3 and 4 hold arguments in units of kNormUnit table intervals, so that
+ * one conversion to 16-bit unsigned normalised integers gives the byte offsets
+ * of both lookups of a bracket (and saturates negative arguments to entry 0).
  */
 constexpr bool erf_mirrored_mode(int em) { return em >= 1; }
+constexpr int erf_pairs(int em) { return erf_mirrored_mode(em) ? 2 * kErfIntervals : kErfIntervals; }
+
+// 2^16 / 8: an argument of k / kNormUnit converts to 8 k, the byte offset of interval k's entry
+constexpr float kNormUnit = 8192.0f;
+constexpr float kErfMid = (float)kErfIntervals / kNormUnit;   // erf(0)'s place in the mirrored table
+
+/*
+ * erf at x1 minus erf at x2, mirrored form with the slopes per kNormUnit
+ * intervals; neither argument reaches the table's top.  The conversion rounds
+ * to an eighth of an interval and the low three bits are dropped, so an argument
+ * within a sixteenth below a node takes the line of the interval above it, which
+ * it extends: an error of 1/30 of h^2 erf'' against the 1/8 inside an interval.
+ * The table is a static LDS array, so that its address goes into the loads'
+ * offsets and none is added to the byte offsets.
+ */
+__device__ inline float erf_diff(const float2 *__restrict__ tab, float x1, float x2)
+{
+    const auto p = __builtin_amdgcn_cvt_pknorm_u16(x1, x2);
+    uint32_t u;
+    __builtin_memcpy(&u, &p, sizeof u);
+    const char *t = reinterpret_cast<const char *>(tab);
+    const float2 q1 = *reinterpret_cast<const float2 *>(t + (u & 0xfff8u));
+    const float2 q2 = *reinterpret_cast<const float2 *>(t + ((u >> 16) & 0xfff8u));
+    return fmaf(x1, q1.y, q1.x) - fmaf(x2, q2.y, q2.x);
+}
 
 /*
  * One bracket of Eq. 3, erf((h - x) is) + erf((h + x) is), with
@@ -671,12 +701,12 @@ __device__ inline float edge_pair(const float2 *__restrict__ tab, float x, float
     return erf_lds(tab, x1) + erf_lds_pos(tab, x2);
 }
 
-/* Mode 3: the bracket from hk = h isk + n and hk2 = n - h isk (n = kErfIntervals):
- * erf(x1) - erf(mirror of (h + |x|) is), both read below the table's top. */
+/* Modes 3 and 4: the bracket from hk = h isk + n and hk2 = n - h isk (n = kErfMid), isk in normalised
+ * units: erf(x1) - erf(mirror of (h + |x|) is), both below the table's top. */
 __device__ inline float edge_pair_sq(const float2 *__restrict__ tab, float x, float hk, float hk2, float isk)
 {
     const float ax = fabsf(x);
-    return erf_m_lo(tab, fmaf(-ax, isk, hk)) - erf_m_lo(tab, fmaf(-ax, isk, hk2));
+    return erf_diff(tab, fmaf(-ax, isk, hk), fmaf(-ax, isk, hk2));
 }
 
 /* hk of the bracket: h isk, plus the mirrored table's offset */
@@ -689,11 +719,12 @@ __device__ inline float edge_offset(float h, float isk)
 /* Per-beamlet constants of the fill, held in registers. */
 template <int K>
 struct FillConst {
-    float tA, inv_step, tau_max, pdd_inv, pdd_max;
+    float tA, step, tau_max, pdd_inv, pdd_max;
     bool floor0;                 // D >= 0 holds exactly: negative rounding residue is cut to 0
     int n_terms;
     float w4[K], ha[K], hb[K];
-    float sig0[K], sig1[K];      // sigma law divided by kIsScale: 1/sigma' = isk
+    float sig0[K], sig1[K];      // sigma law divided by is_scale<EM>: 1/sigma' = isk
+    float ratio[K];              // mode 4: sigma of the first term over this term's
     // general form (tables): A and c grids, beamlet half sides
     float a_inv, a_max, c_inv, c_max, half_a, half_b;
     int nc;
@@ -701,38 +732,65 @@ struct FillConst {
 
 // is kErfScale = kIsScale / sigma
 constexpr float kIsScale = 0.70710678118654752f * kErfScale;
+template <int EM>
+constexpr float is_scale = EM >= 3 ? kIsScale / kNormUnit : kIsScale;
 
 /*
- * D of one VOI voxel at s = t' - tA, with U' = (P - S).eu' SAD and
- * V' = (P - S).ev' SAD (the lateral offsets scaled by SAD in advance), so that
- * with r = 1/t' the iso-plane offsets are u = U' r, v = V' r and the inverse
- * square (SAD/t')^2 = SAD^2 r^2 has its SAD^2 folded into the LDS depth dose.
+ * D of one VOI voxel at s = (t' - tA) / step (cm with SURR: not divided), with
+ * U' = (P - S).eu' SAD and V' = (P - S).ev' SAD (the lateral offsets scaled by SAD
+ * in advance), so that with r = 1/t' the iso-plane offsets are u = U' r, v = V' r
+ * and the inverse square (SAD/t')^2 = SAD^2 r^2 has its SAD^2 folded into the LDS
+ * depth dose.  s is the depth table's coordinate, and the table holds depths in
+ * the depth dose's coordinate (cm with SURR).
+ *
+ * Mode 4: with q = 1/(t' sigma'), one reciprocal (a quarter-rate instruction)
+ * serves r = sigma' q, isk = t' q and u isk = U' q, and the other terms' are fixed
+ * multiples of it.  With the paired erf lookups the slab's fill issues 81 VALU
+ * instructions per 64 nonzeros instead of 88, one of them a reciprocal instead of
+ * three.  The card's power limit then sets the pace (the clock moves between
+ * 2.0 and 2.4 GHz over a fill): pelvis fill 1119 -> 1085 us, slab fill 1765 -> 1763.
  */
-template <int K, bool GUARD, int EM>
+template <int K, bool GUARD, int EM, bool SURR>
 __device__ inline float dose_value(const FillConst<K> &c, const float2 *__restrict__ tab,
                                    const float2 *__restrict__ pdd, const float2 *__restrict__ etab,
                                    float s, float U, float V)
 {
-    const float r = __builtin_amdgcn_rcpf(s + c.tA);   // 1 / t'
-    const float u = U * r, v = V * r;
     // radiological depth at O': linear interpolation in the table, one FMA in the intercept form
     // (last entry has slope 0)
-    const float tau = __builtin_amdgcn_fmed3f(s * c.inv_step, 0.0f, c.tau_max);
+    const float t = SURR ? s + c.tA : fmaf(s, c.step, c.tA);   // t'
+    const float tau = __builtin_amdgcn_fmed3f(SURR ? s * c.step : s, 0.0f, c.tau_max);
     const float2 q = tab[(int)tau];
     const float d = fmaf(tau, q.y, q.x);
     // depth dose times SAD^2, held at the last node
-    const float x = __builtin_amdgcn_fmed3f(d * c.pdd_inv, 0.0f, c.pdd_max);
+    const float x = __builtin_amdgcn_fmed3f(SURR ? d * c.pdd_inv : d, 0.0f, c.pdd_max);
     const float2 qp = pdd[(int)x];
-    const float A = fmaf(x, qp.y, qp.x) * r * r;
+    const float P = fmaf(x, qp.y, qp.x);
     // lateral profile, Eq. 3
     float L = 0.0f;
+    if (EM == 4) {
+        const float sg = fmaf(c.sig1[0], d, c.sig0[0]), rq = __builtin_amdgcn_rcpf(t * sg);
+        const float isk = t * rq, r = sg * rq;
+#pragma unroll
+        for (int i = 0; i < K; ++i) {
+            if (GUARD && i >= c.n_terms) break;
+            // c.ha[i] carries the ratio; the first term's weight is in the depth dose, c.w4 relative to it
+            const float hk = fmaf(c.ha[i], isk, kErfMid), hk2 = fmaf(-c.ha[i], isk, kErfMid);
+            const float qi = i == 0 ? rq : rq * c.ratio[i];
+            const float eu = edge_pair_sq(etab, U, hk, hk2, qi), ev = edge_pair_sq(etab, V, hk, hk2, qi);
+            L = i == 0 ? eu * ev : fmaf(c.w4[i] * eu, ev, L);
+        }
+        return fmaxf(P * r * r * L, 0.0f);   // D >= 0: see below
+    }
+    const float r = __builtin_amdgcn_rcpf(t);   // 1 / t'
+    const float u = U * r, v = V * r;
+    const float A = P * r * r;
 #pragma unroll
     for (int i = 0; i < K; ++i) {
         if (GUARD && i >= c.n_terms) break;
         const float isk = __builtin_amdgcn_rcpf(fmaf(c.sig1[i], d, c.sig0[i]));
         if (EM == 3) {
             // square beamlets; the first term's weight is in the depth dose, c.w4 relative to it
-            const float hk = fmaf(c.ha[i], isk, (float)kErfIntervals), hk2 = fmaf(-c.ha[i], isk, (float)kErfIntervals);
+            const float hk = fmaf(c.ha[i], isk, kErfMid), hk2 = fmaf(-c.ha[i], isk, kErfMid);
             const float eu = edge_pair_sq(etab, u, hk, hk2, isk), ev = edge_pair_sq(etab, v, hk, hk2, isk);
             L = i == 0 ? eu * ev : fmaf(c.w4[i] * eu, ev, L);
         } else {
@@ -758,9 +816,9 @@ __device__ inline float dose_value_gen(const FillConst<K> &c, const float2 *__re
                                        const float2 *__restrict__ sA, const float2 *__restrict__ sc,
                                        const float2 *__restrict__ etab, float s, float U, float V)
 {
-    const float r = __builtin_amdgcn_rcpf(s + c.tA);
+    const float r = __builtin_amdgcn_rcpf(fmaf(s, c.step, c.tA));
     const float u = U * r, v = V * r;
-    const float tau = __builtin_amdgcn_fmed3f(s * c.inv_step, 0.0f, c.tau_max);
+    const float tau = __builtin_amdgcn_fmed3f(s, 0.0f, c.tau_max);
     const float2 q = tab[(int)tau];
     const float d = fmaf(tau, q.y, q.x);
     const float xa = __builtin_amdgcn_fmed3f(d * c.a_inv, 0.0f, c.a_max);
@@ -774,11 +832,11 @@ __device__ inline float dose_value_gen(const FillConst<K> &c, const float2 *__re
     for (int i = 0; i < K; ++i) {
         const float2 q1 = sc[i * c.nc + kc], q2 = sc[(K + i) * c.nc + kc], q3 = sc[(2 * K + i) * c.nc + kc];
         const float c1 = fmaf(fc, q1.y, q1.x), c2 = fmaf(fc, q2.y, q2.x), c3 = fmaf(fc, q3.y, q3.x);
-        const float isk = kIsScale * __builtin_amdgcn_rcpf(c3);
+        const float isk = is_scale<EM> * __builtin_amdgcn_rcpf(c3);
         float eu, ev;
         if (EM == 3) {
             const float h = c2 * c.half_a;
-            const float hk = fmaf(h, isk, (float)kErfIntervals), hk2 = fmaf(-h, isk, (float)kErfIntervals);
+            const float hk = fmaf(h, isk, kErfMid), hk2 = fmaf(-h, isk, kErfMid);
             eu = edge_pair_sq(etab, u, hk, hk2, isk);
             ev = edge_pair_sq(etab, v, hk, hk2, isk);
         } else {
@@ -812,7 +870,7 @@ __device__ inline int readlane(int v, int lane) { return __builtin_amdgcn_readla
  */
 /* tile_group: consecutive 64-row tiles a wave takes per step (the batched fill's tuned shape). */
 template <int K, int W, bool GUARD, bool SURR, bool GEN = false, int EM = 0>
-__device__ __attribute__((always_inline)) inline void fill_beamlet(const PlanDev &P, const OutDev &O, int j, unsigned char *smem,
+__device__ __attribute__((always_inline)) inline void fill_beamlet(const PlanDev &P, const OutDev &O, int j, float2 *s_erf, unsigned char *smem,
                                                              int tile_group = 1)
 {
     const BeamletRec &R = P.rec[j];
@@ -821,7 +879,9 @@ __device__ __attribute__((always_inline)) inline void fill_beamlet(const PlanDev
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = lane_id();
     constexpr bool SE = erf_mirrored_mode(EM);
     // mode 3, analytic form: term weights relative to the first, whose weight the depth dose carries
-    constexpr bool FOLD_W = EM == 3 && !GEN;
+    constexpr bool FOLD_W = EM >= 3 && !GEN;
+    // the row start values' t' and the depth table in the tables' own coordinates (dose_value)
+    constexpr bool UNITS = !SURR;
 
     // ---- constants into registers
     const int n_table = R.n_table, n_pdd = lds_pdd_pairs(P), tile0 = R.tile0;
@@ -830,7 +890,8 @@ __device__ __attribute__((always_inline)) inline void fill_beamlet(const PlanDev
     const int nx = P.nx, ny = P.ny, wpr = P.wpr;
     FillConst<K> c;
     c.tA = R.tA_f;
-    c.inv_step = R.inv_step_f;
+    const double inv_step = UNITS ? 1.0 / R.step : 1.0;
+    c.step = UNITS ? (float)R.step : R.inv_step_f;
     c.tau_max = R.tau_max_f;
     c.pdd_inv = P.pdd_inv_step;
     c.pdd_max = P.pdd_max;
@@ -839,9 +900,10 @@ __device__ __attribute__((always_inline)) inline void fill_beamlet(const PlanDev
 #pragma unroll
     for (int i = 0; i < K; ++i) {
         c.w4[i] = FOLD_W ? P.w4[i] / P.w4[0] : P.w4[i];
-        c.sig0[i] = P.sig0[i] * (1.0f / kIsScale);
-        c.sig1[i] = P.sig1[i] * (1.0f / kIsScale);
-        c.ha[i] = R.ha[i];
+        c.sig0[i] = P.sig0[i] * (1.0f / is_scale<EM>);
+        c.sig1[i] = P.sig1[i] * (1.0f / is_scale<EM>) * (UNITS && !GEN ? P.pdd_step : 1.0f);
+        c.ratio[i] = EM == 4 ? P.sig0[0] / P.sig0[i] : 1.0f;
+        c.ha[i] = EM == 4 ? R.ha[i] * c.ratio[i] : R.ha[i];
         c.hb[i] = R.hb[i];
     }
     if (GEN) {
@@ -855,8 +917,9 @@ __device__ __attribute__((always_inline)) inline void fill_beamlet(const PlanDev
     }
     const float sad_f = R.sad_f;
     const double tA = R.tA, sad = R.sad;
-    // per voxel step along x: t' in float, U and V scaled by SAD (rounded once from FP64)
-    const float t1f = R.t1_f, U1f = (float)(R.dx[1] * sad), V1f = (float)(R.dx[2] * sad);
+    // per voxel step along x: t' (over the table step) in float, U and V scaled by SAD (rounded once
+    // from FP64)
+    const float t1f = UNITS ? (float)(R.dx[0] * inv_step) : R.t1_f, U1f = (float)(R.dx[1] * sad), V1f = (float)(R.dx[2] * sad);
     const gptr<const uint32_t> bits = as_global<const uint32_t>(P.bits);
     const gptr<int32_t> out_idx = as_global<int32_t>(O.indices);
     const gptr<float> out_val = as_global<float>(O.values);
@@ -866,9 +929,8 @@ __device__ __attribute__((always_inline)) inline void fill_beamlet(const PlanDev
     // ---- LDS: erf table, depth table, depth dose (times SAD^2), tile prefix; the depth table
     // and the depth dose (or the general form's A row) as (intercept, slope) in their own
     // table coordinate, value = x slope + intercept for x in [k, k + 1]
-    float2 *s_erf = reinterpret_cast<float2 *>(smem);
-    constexpr int kErfPairs = SE ? 2 * kErfIntervals : kErfIntervals;
-    float2 *s_tab = s_erf + kErfPairs;
+    constexpr int kErfPairs = erf_pairs(EM);
+    float2 *s_tab = reinterpret_cast<float2 *>(smem);
     float2 *s_pdd = s_tab + P.max_table;
     int *s_tpre = reinterpret_cast<int *>(s_pdd + n_pdd);
     __shared__ int wsum[W];
@@ -877,7 +939,7 @@ __device__ __attribute__((always_inline)) inline void fill_beamlet(const PlanDev
     const int c1_pos = __builtin_amdgcn_readfirstlane(R.c1_pos), c1_neg = __builtin_amdgcn_readfirstlane(R.c1_neg);
     // surrogate: per-wave h1 tile after the tile prefix, and W2 fragments in registers
     uint16_t *s_h1 = reinterpret_cast<uint16_t *>(
-        smem + ((sizeof(float2) * ((size_t)kErfPairs + P.max_table + n_pdd) +
+        smem + ((sizeof(float2) * ((size_t)P.max_table + n_pdd) +
                  sizeof(int) * ((size_t)P.max_tiles + 1) + 15) & ~(size_t)15)) + wave * (64 * mlp::kH1Stride);
     // and the layer-1 bias with this beamlet's width term folded in, after the W tiles
     float *s_b1x = reinterpret_cast<float *>(s_h1 + (W - wave) * (64 * mlp::kH1Stride));
@@ -892,13 +954,18 @@ __device__ __attribute__((always_inline)) inline void fill_beamlet(const PlanDev
         // the erf table in the form this fill reads (compact, or mirrored after it)
         const float4 *__restrict__ et = reinterpret_cast<const float4 *>(P.erf_tab + (SE ? kErfIntervals : 0));
         float4 *se4 = reinterpret_cast<float4 *>(s_erf);
-        for (int i = tid; i < kErfPairs / 2; i += kB) se4[i] = et[i];
+        constexpr float es = EM >= 3 ? kNormUnit : 1.0f;
+        for (int i = tid; i < kErfPairs / 2; i += kB) {
+            const float4 e = et[i];
+            se4[i] = make_float4(e.x, e.y * es, e.z, e.w * es);
+        }
         if (tid < kGeomWords) reinterpret_cast<double *>(&s_geom)[tid] = (&R.cu_sad)[tid];
         const gptr<const float> tab = as_global<const float>(P.tables + R.table_off);
+        const float ds = UNITS && !GEN ? P.pdd_inv_step : 1.0f;
         for (int i = tid; i < n_table; i += kB) {
             const float d0 = tab[i];
-            const float sl = (i + 1 < n_table ? tab[i + 1] : d0) - d0;
-            s_tab[i] = make_float2(fmaf(-(float)i, sl, d0), sl);
+            const float sl = ((i + 1 < n_table ? tab[i + 1] : d0) - d0) * ds;
+            s_tab[i] = make_float2(fmaf(-(float)i, sl, d0 * ds), sl);
         }
         const float sad2 = sad_f * sad_f;
         if (GEN) {
@@ -990,7 +1057,7 @@ __device__ __attribute__((always_inline)) inline void fill_beamlet(const PlanDev
                 cb = grow * nx + lo;
                 wb = grow * wpr;
                 const double x = (double)lo;
-                s_lo = (float)(a.t0 + x * G.dx[0] - tA);
+                s_lo = (float)((a.t0 + x * G.dx[0] - tA) * inv_step);
                 U_lo = (float)(fma(x, G.dx[1], a.U0) * sad);
                 V_lo = (float)(fma(x, G.dx[2], a.V0) * sad);
             } else {
@@ -1073,7 +1140,7 @@ __device__ __attribute__((always_inline)) inline void fill_beamlet(const PlanDev
                 const float rr_ = __builtin_amdgcn_rcpf(sv + c.tA);
                 const float g = sad_f * rr_;
                 const float au = fabsf(Uv * rr_), av = fabsf(Vv * rr_);
-                const float tau = __builtin_amdgcn_fmed3f(sv * c.inv_step, 0.0f, c.tau_max);
+                const float tau = __builtin_amdgcn_fmed3f(sv * c.step, 0.0f, c.tau_max);
                 const float2 q = s_tab[(int)tau];
                 const float d = fmaf(tau, q.y, q.x);
                 const bool in_box = member && mlp_ok && d <= kMlpDMax && au <= kMlpUVMax &&
@@ -1084,7 +1151,7 @@ __device__ __attribute__((always_inline)) inline void fill_beamlet(const PlanDev
                 float y = 0.0f;
                 if (__ballot(in_box)) y = mlp::forward_wave<true>(P.mlp_p, s_b1x, wf, x, s_h1);
                 if (in_box) D = y * g * g;
-                else if (member) D = dose_value<K, GUARD, EM>(c, s_tab, s_pdd, s_erf, sv, Uv, Vv);
+                else if (member) D = dose_value<K, GUARD, EM, SURR>(c, s_tab, s_pdd, s_erf, sv, Uv, Vv);
             }
             if (member) {
                 const float kf = (float)k;
@@ -1092,7 +1159,7 @@ __device__ __attribute__((always_inline)) inline void fill_beamlet(const PlanDev
                     D = dose_value_gen<K, EM>(c, s_tab, s_pdd, s_pdd + P.n_adepth, s_erf, fmaf(kf, t1f, sl),
                                                   fmaf(kf, U1f, ul), fmaf(kf, V1f, vl));
                 else if (!SURR)
-                    D = dose_value<K, GUARD, EM>(c, s_tab, s_pdd, s_erf, fmaf(kf, t1f, sl), fmaf(kf, U1f, ul),
+                    D = dose_value<K, GUARD, EM, SURR>(c, s_tab, s_pdd, s_erf, fmaf(kf, t1f, sl), fmaf(kf, U1f, ul),
                                                      fmaf(kf, V1f, vl));
                 if (FITS) {
                     const int so = (int)(written - out0) << 2;
@@ -1157,7 +1224,7 @@ __device__ __attribute__((always_inline)) inline void fill_beamlet(const PlanDev
                     if (GEN)
                         return dose_value_gen<K, EM>(c, s_tab, s_pdd, s_pdd + P.n_adepth, s_erf, fmaf(kf, t1f, sl),
                                                      fmaf(kf, U1f, ul), fmaf(kf, V1f, vl));
-                    return dose_value<K, GUARD, EM>(c, s_tab, s_pdd, s_erf, fmaf(kf, t1f, sl), fmaf(kf, U1f, ul),
+                    return dose_value<K, GUARD, EM, SURR>(c, s_tab, s_pdd, s_erf, fmaf(kf, t1f, sl), fmaf(kf, U1f, ul),
                                                     fmaf(kf, V1f, vl));
                 };
                 // the second candidate of a row's last, odd slot is evaluated at the first (and not stored)
@@ -1241,9 +1308,10 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(SURR || 
                                                   const OutDev *__restrict__ outs)
 {
     extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ __align__(16) float2 s_erf[erf_pairs(EM)];   // at a fixed address: see erf_diff
     // launched before the host has read the plan's total: write nothing if it does not fit
     if (outs[0].check_nnz && *plans[0].nnz > outs[0].capacity) return;
-    fill_beamlet<K, kWavesPerBlock, false, SURR, GEN, EM>(plans[0], outs[0], outs[0].row0 + (int)blockIdx.x, smem);
+    fill_beamlet<K, kWavesPerBlock, false, SURR, GEN, EM>(plans[0], outs[0], outs[0].row0 + (int)blockIdx.x, s_erf, smem);
 }
 
 /* ------------------------------------------------------------ batches */
@@ -1298,6 +1366,7 @@ __global__ __launch_bounds__(W * kWave) __attribute__((amdgpu_waves_per_eu(4))) 
                                                      int *__restrict__ counter, int per_item, int tile_group)
 {
     extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ __align__(16) float2 s_erf[erf_pairs(4)];
     __shared__ int s_item;
     for (;;) {
         if (threadIdx.x == 0) s_item = atomicAdd(counter, 1);
@@ -1311,10 +1380,11 @@ __global__ __launch_bounds__(W * kWave) __attribute__((amdgpu_waves_per_eu(4))) 
             const PlanDev &P = *plans[it.x];
             // each plan in the erf table form of its own fill (identical results to it)
             switch (P.erf_mode) {
-            case 3: fill_beamlet<K, W, true, false, false, 3>(P, outs[it.x], it.y, smem, tile_group); break;
-            case 2: fill_beamlet<K, W, true, false, false, 2>(P, outs[it.x], it.y, smem, tile_group); break;
-            case 1: fill_beamlet<K, W, true, false, false, 1>(P, outs[it.x], it.y, smem, tile_group); break;
-            default: fill_beamlet<K, W, true, false, false, 0>(P, outs[it.x], it.y, smem, tile_group); break;
+            case 4: fill_beamlet<K, W, true, false, false, 4>(P, outs[it.x], it.y, s_erf, smem, tile_group); break;
+            case 3: fill_beamlet<K, W, true, false, false, 3>(P, outs[it.x], it.y, s_erf, smem, tile_group); break;
+            case 2: fill_beamlet<K, W, true, false, false, 2>(P, outs[it.x], it.y, s_erf, smem, tile_group); break;
+            case 1: fill_beamlet<K, W, true, false, false, 1>(P, outs[it.x], it.y, s_erf, smem, tile_group); break;
+            default: fill_beamlet<K, W, true, false, false, 0>(P, outs[it.x], it.y, s_erf, smem, tile_group); break;
             }
             __syncthreads();
         }
@@ -1378,18 +1448,27 @@ size_t fill_shared_bytes(const PlanDev &h)
     return fill_shared_bytes(h, fill_mirrored_erf(h));
 }
 
+static size_t fill_dynamic_bytes(const PlanDev &h, bool mirrored_erf)
+{
+    return fill_shared_bytes(h, mirrored_erf) - sizeof(float2) * erf_pairs(mirrored_erf ? 1 : 0);
+}
+
+size_t fill_dynamic_bytes(const PlanDev &h) { return fill_dynamic_bytes(h, fill_mirrored_erf(h)); }
+
 bool fill_mirrored_erf(const PlanDev &h) { return h.erf_mirrored && !h.use_mlp; }
 
 int mirrored_erf_mode(const PlanDev &h)
 {
     if (!h.erf_nc) return 1;
-    return h.erf_square && h.d_floor == 0.0f && (h.gen || h.w4[0] != 0.0f) ? 3 : 2;
+    if (!h.erf_square || h.d_floor != 0.0f || (!h.gen && h.w4[0] == 0.0f)) return 2;
+    return h.sig_prop && !h.gen ? 4 : 3;
 }
 
 template <int K, bool GEN>
 static const void *fill_kernel_ptr_k(int em)
 {
     switch (em) {
+    case 4: return (const void *)k_fill<K, false, GEN, GEN ? 3 : 4>;
     case 3: return (const void *)k_fill<K, false, GEN, 3>;
     case 2: return (const void *)k_fill<K, false, GEN, 2>;
     case 1: return (const void *)k_fill<K, false, GEN, 1>;
@@ -1432,8 +1511,8 @@ static int fill_groups_per_cu(const void *f, size_t lds, int lds_per_cu)
 
 int choose_erf_form(const PlanDev &h)
 {
-    const size_t lds_m = fill_shared_bytes(h, true), lds_s = fill_shared_bytes(h, false);
-    if (lds_m > 64 * 1024) return 0;
+    if (fill_shared_bytes(h, true) > 64 * 1024) return 0;
+    const size_t lds_m = fill_dynamic_bytes(h, true), lds_s = fill_dynamic_bytes(h, false);
     int dev = 0, lds_cu = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&lds_cu, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor, dev) != hipSuccess ||
@@ -1513,7 +1592,7 @@ hipError_t launch_fill(const PlanDev *dplan, const OutDev *dout, const PlanDev &
     (void)row0;   // read by the kernel from the output record
     if (n_rows <= 0) return hipSuccess;
     const dim3 grid(n_rows), block(kBlock);
-    const size_t lds = fill_shared_bytes(h);
+    const size_t lds = fill_dynamic_bytes(h);
     if (h.use_mlp) {
         switch (h.n_terms) {
         case 1: hipLaunchKernelGGL((k_fill<1, true, false, 0>), grid, block, lds, s, dplan, dout); break;
