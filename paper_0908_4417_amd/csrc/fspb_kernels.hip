@@ -868,10 +868,11 @@ __device__ inline int readlane(int v, int lane) { return __builtin_amdgcn_readla
  * K = unrolled term count; GUARD: stop at P.n_terms (plans of mixed K);
  * EM: how erf is read (erf_mirrored_mode).
  */
-/* tile_group: consecutive 64-row tiles a wave takes per step (the batched fill's tuned shape). */
+/* tile_group: consecutive 64-row tiles a wave takes per step (the batched fill's tuned shape);
+ * part, parts: this workgroup's share of the beamlet, the part-th W of every parts W steps. */
 template <int K, int W, bool GUARD, bool SURR, bool GEN = false, int EM = 0>
 __device__ __attribute__((always_inline)) inline void fill_beamlet(const PlanDev &P, const OutDev &O, int j, float2 *s_erf, unsigned char *smem,
-                                                             int tile_group = 1)
+                                                             int tile_group = 1, int part = 0, int parts = 1)
 {
     const BeamletRec &R = P.rec[j];
     if (R.n_tiles == 0) return;   // the axis misses the grid
@@ -1022,10 +1023,11 @@ __device__ __attribute__((always_inline)) inline void fill_beamlet(const PlanDev
         __syncthreads();
     }
 
-    // the wave's tiles: runs of tile_group consecutive tiles, every W-th run.  Lane = a grid
+    // the wave's tiles: runs of tile_group consecutive tiles, every (parts W)-th run.  Lane = a grid
     // row r of the beamlet's row block (of a block tile, or an entry of the row list); with the
     // list, the next tile's entries are loaded while this tile is walked
-    auto next_tile = [&](int t) { return (t + 1) % tile_group != 0 ? t + 1 : t + 1 + (W - 1) * tile_group; };
+    const int first_tile = (part * W + wave) * tile_group, stride = parts * W;
+    auto next_tile = [&](int t) { return (t + 1) % tile_group != 0 ? t + 1 : t + 1 + (stride - 1) * tile_group; };
     auto list_entry = [&](int t) {
         const int li = t * kRowsPerTile + lane;
         return t < n_tiles && li < n_list ? row_list[li] : -1;
@@ -1288,14 +1290,14 @@ __device__ __attribute__((always_inline)) inline void fill_beamlet(const PlanDev
         }
     };
     if (!use_list) {
-        for (int tg = wave * tile_group; tg < n_tiles; tg += W * tile_group)
+        for (int tg = first_tile; tg < n_tiles; tg += stride * tile_group)
             for (int tl = tg; tl < tg + tile_group && tl < n_tiles; ++tl) {
                 const int r = tl * kRowsPerTile + lane;
                 tile(tl, r < n_list ? r : -1, [] {});
             }
     } else {
-        int r_next = list_entry(wave * tile_group);
-        for (int tl = wave * tile_group; tl < n_tiles; tl = next_tile(tl)) {
+        int r_next = list_entry(first_tile);
+        for (int tl = first_tile; tl < n_tiles; tl = next_tile(tl)) {
             const int r = r_next;
             tile(tl, r, [&] { r_next = list_entry(next_tile(tl)); });
         }
@@ -1311,7 +1313,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(SURR || 
     __shared__ __align__(16) float2 s_erf[erf_pairs(EM)];   // at a fixed address: see erf_diff
     // launched before the host has read the plan's total: write nothing if it does not fit
     if (outs[0].check_nnz && *plans[0].nnz > outs[0].capacity) return;
-    fill_beamlet<K, kWavesPerBlock, false, SURR, GEN, EM>(plans[0], outs[0], outs[0].row0 + (int)blockIdx.x, s_erf, smem);
+    fill_beamlet<K, kWavesPerBlock, false, SURR, GEN, EM>(plans[0], outs[0], outs[0].row0 + (int)blockIdx.x, s_erf, smem, 1,
+                                                         (int)blockIdx.y, (int)gridDim.y);
 }
 
 /* ------------------------------------------------------------ batches */
@@ -1586,12 +1589,26 @@ hipError_t launch_batch_fill(int K, int W, const PlanDev *const *plans, const Ou
     }
 }
 
+/*
+ * Workgroups per beamlet of a plan's fill: with a workgroup each, a plan of few beamlets leaves
+ * CUs idle or ends in a ragged last round (100 beamlets: fill 23 us in 6 parts against 53; 715 with
+ * the three-term kernel: the whole plan 224 us in 5 parts against 268), while a plan of many gains
+ * nothing and stages every table twice (5184 beamlets: 1.264 ms in 3 parts against 1.248, 1.434
+ * in 10).  No more parts than a beamlet has sets of tiles.
+ */
+constexpr int kFillGroups = 5000;
+static unsigned fill_parts(const PlanDev &h, int n_rows)
+{
+    const int most = std::max(1, h.max_tiles / kWavesPerBlock);
+    return (unsigned)std::min(most, std::max(1, (kFillGroups + n_rows - 1) / n_rows));
+}
+
 hipError_t launch_fill(const PlanDev *dplan, const OutDev *dout, const PlanDev &h, int row0, int n_rows,
                        hipStream_t s)
 {
     (void)row0;   // read by the kernel from the output record
     if (n_rows <= 0) return hipSuccess;
-    const dim3 grid(n_rows), block(kBlock);
+    const dim3 grid(n_rows, fill_parts(h, n_rows)), block(kBlock);
     const size_t lds = fill_dynamic_bytes(h);
     if (h.use_mlp) {
         switch (h.n_terms) {

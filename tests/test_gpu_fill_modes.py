@@ -38,7 +38,7 @@ CASES = [(k, (41, 37, 23), (0.5, 0.45, 0.55), 3, 3, 2, "slab") for k in KERNELS]
     ("twofold", (9, 7, 1), (0.5, 0.5, 0.5), 1, 1, 1, "slab"),
     ("twofold", (150, 160, 40), (0.2, 0.2, 0.3), 1, 1, 1, "slab"),
     ("twofold", (90, 96, 30), (0.5, 0.4, 0.6), 2, 2, 3, "pelvis"),
-    ("twofold", (20, 20, 12), (1.0, 1.0, 1.0), 9, 24, 24, "slab"),
+    ("twofold", (20, 20, 18), (1.0, 1.0, 1.0), 9, 24, 24, "slab"),   # every axis meets the grid
 ]
 
 
