@@ -938,18 +938,16 @@ __device__ __attribute__((always_inline)) inline void fill_beamlet(const PlanDev
     // the beamlet's VOI row coefficients, read by every tile (LDS keeps them out of registers)
     __shared__ RowGeom s_geom;
     const int c1_pos = __builtin_amdgcn_readfirstlane(R.c1_pos), c1_neg = __builtin_amdgcn_readfirstlane(R.c1_neg);
-    // surrogate: per-wave h1 tile after the tile prefix, and W2 fragments in registers
-    uint16_t *s_h1 = reinterpret_cast<uint16_t *>(
-        smem + ((sizeof(float2) * ((size_t)P.max_table + n_pdd) +
-                 sizeof(int) * ((size_t)P.max_tiles + 1) + 15) & ~(size_t)15)) + wave * (64 * mlp::kH1Stride);
-    // and the layer-1 bias with this beamlet's width term folded in, after the W tiles
-    float *s_b1x = reinterpret_cast<float *>(s_h1 + (W - wave) * (64 * mlp::kH1Stride));
+    // surrogate: its parameters after the tile prefix, the beamlet's width term in the first bias,
+    // and W2 fragments in registers
+    mlp::Weights &s_mlp = *reinterpret_cast<mlp::Weights *>(
+        smem + ((sizeof(float2) * ((size_t)P.max_table + n_pdd) + sizeof(int) * ((size_t)P.max_tiles + 1) + 15) &
+                ~(size_t)15));
     mlp::W2Frags wf;
     if (SURR) mlp::load_w2_frags(P.mlp_w2, wf);
-    const float a_f = R.a_f;
+    const float a_f = R.a_f, mlp_b3 = SURR ? P.mlp_p[kOffB3] : 0.0f;
     const bool mlp_ok = SURR && R.mlp_ok;
-    if (SURR && tid < kMlpH)
-        s_b1x[tid] = fmaf(P.mlp_p[kOffW1 + tid * kMlpIn + 3], mlp::feature_a(a_f), P.mlp_p[kOffB1 + tid]);
+    if (SURR) mlp::stage_weights<true>(s_mlp, P.mlp_p, mlp::feature_a(a_f), tid, kB);
 
     {
         // the erf table in the form this fill reads (compact, or mirrored after it)
@@ -1151,7 +1149,7 @@ __device__ __attribute__((always_inline)) inline void fill_beamlet(const PlanDev
                 if (in_box) mlp::features(d, au, av, a_f, x);
                 // the network only for chunks with a sample inside the training box
                 float y = 0.0f;
-                if (__ballot(in_box)) y = mlp::forward_wave<true>(P.mlp_p, s_b1x, wf, x, s_h1);
+                if (__ballot(in_box)) y = mlp::forward_wave<true>(s_mlp, wf, x) + mlp_b3;
                 if (in_box) D = y * g * g;
                 else if (member) D = dose_value<K, GUARD, EM, SURR>(c, s_tab, s_pdd, s_erf, sv, Uv, Vv);
             }
@@ -1304,9 +1302,10 @@ __device__ __attribute__((always_inline)) inline void fill_beamlet(const PlanDev
     }
 }
 
-// the analytic form's register budget at one or two terms: six waves per SIMD (80 VGPRs)
+// the analytic form's register budget at one or two terms: six waves per SIMD (80 VGPRs); the
+// surrogate's: two, so that at most 256 registers are used and none lies in the accumulation file
 template <int K, bool SURR, bool GEN, int EM>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(SURR || GEN || K > 2 ? 1 : 6))) void k_fill(const PlanDev *__restrict__ plans,
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(SURR ? 2 : GEN || K > 2 ? 1 : 6))) void k_fill(const PlanDev *__restrict__ plans,
                                                   const OutDev *__restrict__ outs)
 {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -1441,8 +1440,7 @@ size_t fill_shared_bytes(const PlanDev &h, bool mirrored_erf)
                                  (size_t)lds_pdd_pairs(h)) +
                sizeof(int) * ((size_t)h.max_tiles + 1);
     if (h.use_mlp)
-        b = ((b + 15) & ~(size_t)15) + sizeof(uint16_t) * 64 * mlp::kH1Stride * kWavesPerBlock +
-            sizeof(float) * kMlpH;
+        b = ((b + 15) & ~(size_t)15) + sizeof(mlp::Weights);
     return b;
 }
 

@@ -66,18 +66,19 @@ __global__ __launch_bounds__(256) void k_mlp_targets(MlpTargetDev K, const float
     targets[i] = pdd * L;
 }
 
-__global__ __launch_bounds__(256) void k_mlp_forward(MlpDev m, const float *__restrict__ feats, int64_t n,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_mlp_forward(MlpDev m, const float *__restrict__ feats, int64_t n,
                                                      float *__restrict__ out)
 {
-    __shared__ __align__(16) uint16_t h1[4][64 * kH1Stride];
-    const int w = threadIdx.x >> 6, l = lane();
-    const int64_t i = ((int64_t)blockIdx.x * 4 + w) * 64 + l;
+    __shared__ __align__(16) Weights W;
+    stage_weights<false>(W, m.p, 0.0f, threadIdx.x, 256);
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     W2Frags wf;
     load_w2_frags(m.w2, wf);
     float x[4] = {0.0f, 0.0f, 0.0f, 0.0f};
     if (i < n)
         for (int k = 0; k < 4; ++k) x[k] = feats[4 * i + k];
-    const float y = forward_wave<false>(m.p, nullptr, wf, x, h1[w]);
+    __syncthreads();
+    const float y = forward_wave<false>(W, wf, x) + m.p[kOffB3];
     if (i < n) out[i] = y;
 }
 

@@ -43,7 +43,7 @@ __device__ inline f32x4 mfma(const bf16x8 &a, const bf16x8 &b, const f32x4 &c)
 
 __device__ inline bf16x8 frag(const uint16_t *p) { return *reinterpret_cast<const bf16x8 *>(p); }
 
-/* B fragments of W2^T for the forward product h1 W2^T: b[ct][ks] covers outputs
+/* Fragments of W2 (A operand of W2 h1^T, and B operand of h1 W2^T): b[ct][ks] covers outputs
  * 16 ct .. 16 ct + 15 and inputs 32 ks .. 32 ks + 31. */
 struct W2Frags {
     bf16x8 b[4][2];
@@ -69,69 +69,107 @@ __device__ inline void features(float d, float au, float av, float a, float x[4]
 }
 
 /*
- * Forward pass of 64 samples, sample = lane, features x.  h1s: this wave's
- * [64][kH1Stride] BF16 LDS tile.  p: FP32 parameters.  With FOLD the fourth
- * feature is the same for every sample and b1x (LDS) holds the layer-1 bias
- * with its term added, b1 + W1[:, 3] x[3]; x[3] is then not read.  Returns the
- * output for the lane's sample.  Every lane of the wave must call it.
+ * The FP32 parameters of the forward pass as it reads them (LDS), built by
+ * stage_weights with every thread of the workgroup.
+ */
+struct Weights {
+    float4 w1[kMlpH];      // W1[o][0..2] and, with FOLD, the bias with the fourth input's term added; else W1[o][3]
+    float b1[kMlpH];       // not with FOLD
+    alignas(16) float b2[kMlpH], w3[kMlpH];
+};
+
+template <bool FOLD>
+__device__ inline void stage_weights(Weights &W, const float *__restrict__ p, float x3, int tid, int n_threads)
+{
+    for (int o = tid; o < kMlpH; o += n_threads) {
+        const float *w = p + kOffW1 + o * kMlpIn;
+        W.w1[o] = make_float4(w[0], w[1], w[2], FOLD ? fmaf(w[3], x3, p[kOffB1 + o]) : w[3]);
+        W.b1[o] = p[kOffB1 + o];
+        W.b2[o] = p[kOffB2 + o];
+        W.w3[o] = p[kOffW3 + o];
+    }
+}
+
+__device__ inline uint32_t bf16_pair(float a, float b)
+{
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    const bf16x2 q = __builtin_convertvector((f32x2){a, b}, bf16x2);
+    uint32_t u;
+    __builtin_memcpy(&u, &q, sizeof u);
+    return u;
+}
+
+/*
+ * Forward pass of 64 samples, sample = lane, features x.  With FOLD the fourth
+ * feature is the same for every sample and folded into W (x[3] is not read).
+ * Returns the output for the lane's sample, without the last bias.  Every lane
+ * of the wave must call it.
+ *
+ * Layer 2 is computed as W2 h1^T, so that h1 is its B operand: lane (g, n)
+ * makes the 16 hidden values of sample n of a tile that it supplies itself
+ * (inputs 32 ks + 8 g + i) and h1 needs neither LDS nor a transpose; the results
+ * of a sample lie in four lanes, so the last layer's sum takes two exchanges per
+ * 16 samples.  Weights are read from LDS once for all four tiles.  Bound by the
+ * 256 quarter-rate instructions of the 128 SiLUs per sample: FIGURES
  */
 template <bool FOLD>
-__device__ inline float forward_wave(const float *__restrict__ p, const float *b1x, const W2Frags &wf,
-                                     const float x[4], uint16_t *h1s)
+__device__ inline float forward_wave(const Weights &W, const W2Frags &wf, const float x[4])
 {
-    const int l = lane();
-    // layer 1 (FP32), h1 rounded to BF16 into the lane's row
-#pragma unroll 4
-    for (int o = 0; o < kMlpH; o += 2) {
-        float z0 = FOLD ? b1x[o] : p[kOffB1 + o], z1 = FOLD ? b1x[o + 1] : p[kOffB1 + o + 1];
+    constexpr int kX = FOLD ? kMlpIn - 1 : kMlpIn;
+    const int l = lane(), n = l & 15, g = l >> 4;
+    float xs[4][kX];
 #pragma unroll
-        for (int k = 0; k < (FOLD ? kMlpIn - 1 : kMlpIn); ++k) {
-            z0 = fmaf(p[kOffW1 + o * kMlpIn + k], x[k], z0);
-            z1 = fmaf(p[kOffW1 + (o + 1) * kMlpIn + k], x[k], z1);
-        }
-        const uint32_t pk = (uint32_t)bf16_bits(z0 * sigmoid(z0)) | ((uint32_t)bf16_bits(z1 * sigmoid(z1)) << 16);
-        *reinterpret_cast<uint32_t *>(h1s + l * kH1Stride + o) = pk;
-    }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    // layer 2 on matrix cores, layer 3 as a dot over each lane's columns + 16-lane reduction
-    const int n = l & 15, g = l >> 4;
-    float y = 0.0f;
+    for (int st = 0; st < 4; ++st)
 #pragma unroll
-    for (int rt = 0; rt < 4; ++rt) {
-        f32x4 acc[4];
+        for (int k = 0; k < kX; ++k) xs[st][k] = __shfl(x[k], 16 * st + n, 64);
+    // layer 1 (FP32), h1 rounded to BF16
+    uint32_t h[4][2][4];
 #pragma unroll
-        for (int ct = 0; ct < 4; ++ct) acc[ct] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
-        for (int ks = 0; ks < 2; ++ks) {
-            const bf16x8 a = frag(h1s + (16 * rt + n) * kH1Stride + 32 * ks + 8 * g);
+        for (int i = 0; i < 4; ++i) {
+            const int o = 32 * ks + 8 * g + 2 * i;
+            const float4 wa = W.w1[o], wb = W.w1[o + 1];
+            const float ba = FOLD ? wa.w : W.b1[o], bb = FOLD ? wb.w : W.b1[o + 1];
 #pragma unroll
-            for (int ct = 0; ct < 4; ++ct) acc[ct] = mfma(a, wf.b[ct][ks], acc[ct]);
-        }
-        float part[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-        for (int ct = 0; ct < 4; ++ct) {
-            const float b2 = p[kOffB2 + 16 * ct + n], w3 = p[kOffW3 + 16 * ct + n];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const float z = acc[ct][i] + b2;
-                part[i] = fmaf(z * sigmoid(z), w3, part[i]);
+            for (int st = 0; st < 4; ++st) {
+                float za = fmaf(wa.z, xs[st][2], fmaf(wa.y, xs[st][1], fmaf(wa.x, xs[st][0], ba)));
+                float zb = fmaf(wb.z, xs[st][2], fmaf(wb.y, xs[st][1], fmaf(wb.x, xs[st][0], bb)));
+                if (!FOLD) {
+                    za = fmaf(wa.w, xs[st][kX - 1], za);
+                    zb = fmaf(wb.w, xs[st][kX - 1], zb);
+                }
+                h[st][ks][i] = bf16_pair(za * sigmoid(za), zb * sigmoid(zb));
             }
         }
+    // layer 2 on the matrix cores, layer 3 as a sum over each lane's 16 outputs
+    float part[4] = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+    for (int ct = 0; ct < 4; ++ct) {
+        const f32x4 b2 = *reinterpret_cast<const f32x4 *>(&W.b2[16 * ct + 4 * g]);
+        const f32x4 w3 = *reinterpret_cast<const f32x4 *>(&W.w3[16 * ct + 4 * g]);
 #pragma unroll
-            for (int m = 1; m < 16; m <<= 1) part[i] += __shfl_xor(part[i], m, 64);
-        // row 16 rt + 4 g' + i is held by the lanes of group g'; lane 16 rt + q wants q = 4 g' + i
-        const int src = 16 * ((l & 15) >> 2);
-        const float v0 = __shfl(part[0], src, 64), v1 = __shfl(part[1], src, 64);
-        const float v2 = __shfl(part[2], src, 64), v3 = __shfl(part[3], src, 64);
-        const int q = l & 3;
-        const float mine = q == 0 ? v0 : (q == 1 ? v1 : (q == 2 ? v2 : v3));
-        if (g == rt) y = mine;
+        for (int st = 0; st < 4; ++st) {
+            f32x4 z = b2;
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks) {
+                bf16x8 q;
+                __builtin_memcpy(&q, h[st][ks], sizeof q);
+                z = mfma(wf.b[ct][ks], q, z);
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) part[st] = fmaf(z[i] * sigmoid(z[i]), w3[i], part[st]);
+        }
     }
-    return y + p[kOffB3];
+    float y = 0.0f;
+#pragma unroll
+    for (int st = 0; st < 4; ++st) {
+        part[st] += __shfl_xor(part[st], 16, 64);
+        part[st] += __shfl_xor(part[st], 32, 64);
+        y = g == st ? part[st] : y;
+    }
+    return y;
 }
 
 }  // namespace mlp
