@@ -119,7 +119,8 @@ const std::vector<float2> &fill_erf_table();
 /*
  * Pinned 64-byte host slots, one per plan, that a plan's nonzero count is
  * copied back into: an asynchronous copy into pinned memory lets
- * fspb_dose_coeffs queue the fill before it waits for the count.  Slots are
+ * fspb_dose_coeffs queue the fill before it waits for the count; and one per
+ * surrogate, that a gradient's kernel writes its loss to.  Slots are
  * carved from pinned pages and recycled; the pages are kept until the process
  * ends.
  */
@@ -1537,6 +1538,11 @@ struct fspb_surrogate {
     int32_t n_terms = 0;
     double weight[4] = {}, sigma0[4] = {}, sigma_slope[4] = {}, width_scale[4] = {}, pdd_step = 0.0;
     std::vector<float> pdd;
+    int64_t *loss_host = nullptr;   // pinned slot fspb_surrogate_gradient reads the loss from
+    ~fspb_surrogate()
+    {
+        if (loss_host) slot_release(loss_host);
+    }
 };
 
 namespace {
@@ -1604,6 +1610,8 @@ fspb_status fspb_surrogate_create(const fspb_kernel *K, const float *init, int32
     fspb_surrogate *s = new (std::nothrow) fspb_surrogate;
     if (!s) return fail(FSPB_ERR_NOMEM, "cannot allocate the surrogate");
     std::unique_ptr<fspb_surrogate> guard(s);
+    fspb_status ss = slot_acquire(&s->loss_host);
+    if (ss != FSPB_OK) return ss;
     char *ws = static_cast<char *>(workspace);
     s->params = reinterpret_cast<float *>(ws + o_p);
     s->m1 = reinterpret_cast<float *>(ws + o_m1);
@@ -1677,12 +1685,11 @@ fspb_status fspb_surrogate_gradient(fspb_surrogate *s, const float *features, co
     FSPB_HIP(fspb::launch_mlp_grad(mlp_view(s), features, targets, n, 0, n, 1, 0, 1.0f / (float)n, s->partials, st),
              "launch gradient");
     FSPB_HIP(fspb::launch_mlp_reduce(s->params, s->m1, s->m2, s->w2, s->w2t, s->partials, waves, 0, 0.f, 0.f, 0.f, 0.f,
-                                     1.f, 1.f, s->grad, st),
+                                     1.f, 1.f, grad, reinterpret_cast<float *>(s->loss_host), st),
              "launch reduce");
-    FSPB_HIP(hipMemcpyAsync(grad, s->grad, sizeof(float) * fspb::kMlpParams, hipMemcpyDeviceToDevice, st), "copy gradient");
-    float lsum = 0.0f;
-    FSPB_HIP(hipMemcpyAsync(&lsum, s->grad + fspb::kMlpParams, sizeof(float), hipMemcpyDeviceToHost, st), "read loss");
     FSPB_HIP(hipStreamSynchronize(st), "synchronise gradient");
+    float lsum;   // written by the kernel: the slot is pinned
+    std::memcpy(&lsum, s->loss_host, sizeof lsum);
     *loss = lsum / (float)n;
     return FSPB_OK;
 }
@@ -1721,7 +1728,7 @@ fspb_status fspb_surrogate_train(fspb_surrogate *s, const float *features, const
                      "launch gradient");
             FSPB_HIP(fspb::launch_mlp_reduce(s->params, s->m1, s->m2, s->w2, s->w2t, s->partials, waves, 1, lr,
                                              cfg->beta1, cfg->beta2, cfg->eps, bc1, bc2,
-                                             b == steps - 1 ? s->grad : nullptr, st),
+                                             b == steps - 1 ? s->grad : nullptr, nullptr, st),
                      "launch Adam");
         }
         float lsum = 0.0f;

@@ -31,7 +31,7 @@ constexpr int kOffB2 = kOffW2 + kMlpH * kMlpH;
 constexpr int kOffW3 = kOffB2 + kMlpH;
 constexpr int kOffB3 = kOffW3 + kMlpH;
 constexpr int kMlpParams = kOffB3 + 1;          // 4545
-constexpr int kPartialStride = 4608;            // per-wave gradient partials (+ loss at kMlpParams)
+constexpr int kPartialStride = 4608;            // gradient partials of 64 samples (+ loss at kMlpParams)
 
 // training-box limits of the surrogate's inputs
 constexpr float kMlpDMax = 30.0f;
@@ -58,15 +58,15 @@ hipError_t launch_mlp_targets(const MlpTargetDev &k, const float *samples, int64
                               float *targets, hipStream_t s);
 hipError_t launch_mlp_forward(const MlpDev &m, const float *features, int64_t n, float *out, hipStream_t s);
 /* One step's gradient partials: sample i of the step is permuted index
- * (offset + (base + i) * stride) mod n_total; n_step samples in 64-sample waves. */
+ * (offset + (base + i) * stride) mod n_total; 64 samples per partial. */
 hipError_t launch_mlp_grad(const MlpDev &m, const float *features, const float *targets, int64_t n_total,
                            int64_t base, int64_t n_step, uint64_t stride, uint64_t offset, float inv_count,
                            float *partials, hipStream_t s);
-/* Reduce partials of n_waves waves; with adam != 0 update params/m/v and the
- * BF16 copies, else write the summed gradient and loss to grad_out. */
+/* Reduce n_part partials; with adam != 0 update params/m/v and the BF16 copies.  grad_out (may be
+ * NULL): the summed gradient, and the loss sum at index kMlpParams unless loss_out is given. */
 hipError_t launch_mlp_reduce(float *params, float *m1, float *m2, uint16_t *w2, uint16_t *w2t,
-                             const float *partials, int n_waves, int adam, float lr, float b1, float b2,
-                             float eps, float bc1, float bc2, float *grad_out, hipStream_t s);
+                             const float *partials, int n_part, int adam, float lr, float b1, float b2,
+                             float eps, float bc1, float bc2, float *grad_out, float *loss_out, hipStream_t s);
 hipError_t launch_mlp_bf16_copies(const float *params, uint16_t *w2, uint16_t *w2t, hipStream_t s);
 
 }  // namespace fspb
