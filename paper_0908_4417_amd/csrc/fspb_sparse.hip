@@ -21,7 +21,7 @@
  *       rows in any order: k_key_count + scan (pointers), k_place_any
  *     entry path (short stretches): k_key_count + scan, k_expand_rows, then
  *       k_rs_hist, scan, k_rs_scatter per 8 bits of the column
- *     k_voxel_dose        dose_i = sum_j D_ij w_j, fixed order  -- 16 lanes per voxel row
+ *     k_voxel_dose        dose_i = sum_j D_ij w_j, fixed order  -- 8 lanes per voxel row
  *
  * Both sorts are stable and the input rows are in ascending beamlet order, so
  * every voxel row lists its beamlets in ascending order: the transpose is
@@ -457,65 +457,115 @@ __global__ __launch_bounds__(kBlock) void k_fluence_gradient(const int64_t *__re
     }
 }
 
-/* dose_i = sum_j D_ij w_j over voxel row i: 16 lanes per row, 16-byte loads of
- * four consecutive entries per lane, the next step's loads in flight while
- * this step's gathers of w are awaited; lane-strided partial sums and a fixed
- * 16-lane butterfly.  Beamlets outside [0, n_w) are skipped. */
-__global__ __launch_bounds__(kBlock) void k_voxel_dose(const int64_t *__restrict__ t_indptr,
-                                                       const int32_t *__restrict__ t_indices,
-                                                       const float *__restrict__ t_values, int n_voxels, int n_w,
-                                                       const float *__restrict__ w, float *__restrict__ dose)
+/*
+ * dose_i = sum_j D_ij w_j over voxel row i, in a fixed order: 8 lanes per row,
+ * steps of 32 entries by 16-byte loads of four consecutive ones per lane, the
+ * next step's loads in flight while this step's entries are added; a row's head,
+ * tail and first step are loaded together, and the pointers of the next row
+ * before them.  Lane-strided partial sums, a fixed butterfly.  Beamlets outside
+ * [0, n_w) are skipped.
+ *
+ * Bound by the read of D.  Neighbouring rows and steps share cache lines, so the
+ * loads are not marked as streamed (16 lanes: 1148 us, marked 1214).  8 lanes,
+ * because many rows are shorter than a step of 16 or 32 (64x64x64, one beam of
+ * 100: 8 us, 13 with 16 lanes, 25 with 32).  w comes from LDS where a CU can hold
+ * four copies and so all its waves (128^3, 9 beams of 900: 1020 us, gathered
+ * through the cache 1202; 12500 beamlets 117 and 102), and workgroups stay for
+ * many rows: 8191 of them (the slab with 4095: 1082 us, 8191: 1028, 12287: 1016; a
+ * pelvis 910, 896, 1016), an odd number, so that no workgroup's rows keep the same
+ * place in the grid's lines (a pelvis with 8192: 1231).
+ * 128^3, 9 beams of 900, 6.5e8 entries: 1028 us (5.1 TB/s), 1469 with 16 lanes per
+ * row, a workgroup per 16 rows, the tail after the steps and w from the cache;
+ * 256x256x100, 9 beams of 576: 1916 -> 896.
+ */
+constexpr int kVoxelBlock = 512;
+constexpr int kVoxelLanes = 8;
+constexpr int kVoxelRows = kVoxelBlock / kVoxelLanes;
+constexpr int kVoxelStep = 4 * kVoxelLanes;
+constexpr int kVoxelLdsWords = 10240;              // 40 KB: four workgroups, 32 waves per CU
+constexpr int kVoxelGroups = 8191;
+template <bool LDS>
+__global__ __launch_bounds__(kVoxelBlock) void k_voxel_dose(const int64_t *__restrict__ t_indptr,
+                                                            const int32_t *__restrict__ t_indices,
+                                                            const float *__restrict__ t_values, int n_voxels, int n_w,
+                                                            const float *__restrict__ w, float *__restrict__ dose)
 {
-    const int64_t i = ((int64_t)blockIdx.x * kBlock + threadIdx.x) >> 4;
-    const int l = threadIdx.x & 15;
+    extern __shared__ float s_w[];
+    if (LDS) {
+        for (int j = threadIdx.x; j < n_w; j += kVoxelBlock) s_w[j] = w[j];
+        __syncthreads();
+    }
+    const float *wt = LDS ? s_w : w;
+    const int l = threadIdx.x & (kVoxelLanes - 1);
     const uint32_t n = (uint32_t)n_w;
-    float acc0 = 0.0f, acc1 = 0.0f;
-    if (i < n_voxels) {
-        // 16-byte loads of four consecutive entries per lane (64 per step), head and tail lane-strided
-        const int64_t e0 = t_indptr[i], e1 = t_indptr[i + 1];
-        const RowSplit sp = row_split(t_indices, t_values, e0, e1, 64);
-        if (e0 + l < sp.a) {
-            const uint32_t j = (uint32_t)t_indices[e0 + l];
-            if (j < n) acc0 = fmaf(t_values[e0 + l], w[j], acc0);
+    const int64_t stride = (int64_t)gridDim.x * kVoxelRows;
+    int64_t i = (int64_t)blockIdx.x * kVoxelRows + threadIdx.x / kVoxelLanes;
+    if (i >= n_voxels) return;
+    int64_t e0 = t_indptr[i], e1 = t_indptr[i + 1];
+    for (;;) {
+        const int64_t in = i + stride;
+        int64_t n0 = 0, n1 = 0;
+        if (in < n_voxels) {
+            n0 = t_indptr[in];
+            n1 = t_indptr[in + 1];
         }
-        // the next step's indices and values are loaded after this step's gathers of w are
-        // issued (non-temporal: streamed once), so they are in flight while those are awaited
-        int64_t e = sp.a + 4 * l;
+        const RowSplit sp = row_split(t_indices, t_values, e0, e1, kVoxelStep);
+        uint32_t hi = ~0u, ti[4];
+        float hv, tv[4];
+        if (e0 + l < sp.a) {
+            hi = (uint32_t)t_indices[e0 + l];
+            hv = t_values[e0 + l];
+        }
+        int64_t e = sp.a + 4 * l, te = sp.b + l;
+        vi4 a;
+        vf4 c;
         if (e < sp.b) {
-            vi4 a = __builtin_nontemporal_load(reinterpret_cast<const vi4 *>(t_indices + e));
-            vf4 c = __builtin_nontemporal_load(reinterpret_cast<const vf4 *>(t_values + e));
-            for (;;) {
-                const int64_t en = e + 64;
-                float x0 = 0.0f, x1 = 0.0f, x2 = 0.0f, x3 = 0.0f;
-                if ((uint32_t)a.x < n) x0 = w[(uint32_t)a.x];
-                if ((uint32_t)a.y < n) x1 = w[(uint32_t)a.y];
-                if ((uint32_t)a.z < n) x2 = w[(uint32_t)a.z];
-                if ((uint32_t)a.w < n) x3 = w[(uint32_t)a.w];
-                vi4 a1 = a;
-                vf4 c1 = c;
-                if (en < sp.b) {
-                    a1 = __builtin_nontemporal_load(reinterpret_cast<const vi4 *>(t_indices + en));
-                    c1 = __builtin_nontemporal_load(reinterpret_cast<const vf4 *>(t_values + en));
-                }
-                if ((uint32_t)a.x < n) acc1 = fmaf(c.x, x0, acc1);
-                if ((uint32_t)a.y < n) acc1 = fmaf(c.y, x1, acc1);
-                if ((uint32_t)a.z < n) acc1 = fmaf(c.z, x2, acc1);
-                if ((uint32_t)a.w < n) acc1 = fmaf(c.w, x3, acc1);
-                if (en >= sp.b) break;
-                a = a1;
-                c = c1;
-                e = en;
+            a = *reinterpret_cast<const vi4 *>(t_indices + e);
+            c = *reinterpret_cast<const vf4 *>(t_values + e);
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            ti[u] = ~0u;
+            if (te + kVoxelLanes * u < e1) {
+                ti[u] = (uint32_t)t_indices[te + kVoxelLanes * u];
+                tv[u] = t_values[te + kVoxelLanes * u];
             }
         }
-        for (int64_t e = sp.b + l; e < e1; e += 16) {
-            const uint32_t j = (uint32_t)t_indices[e];
-            if (j < n) acc0 = fmaf(t_values[e], w[j], acc0);
-        }
-    }
-    float s = acc0 + acc1;
+        float acc[2] = {0.0f, 0.0f};
+        while (e < sp.b) {
+            e += kVoxelStep;
+            float x[4];
 #pragma unroll
-    for (int d = 8; d > 0; d >>= 1) s += __shfl_xor(s, d, kWave);
-    if (l == 0 && i < n_voxels) dose[i] = s;
+            for (int u = 0; u < 4; ++u)
+                if ((uint32_t)a[u] < n) x[u] = wt[(uint32_t)a[u]];
+            const vi4 ap = a;
+            const vf4 cp = c;
+            if (e < sp.b) {
+                a = *reinterpret_cast<const vi4 *>(t_indices + e);
+                c = *reinterpret_cast<const vf4 *>(t_values + e);
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if ((uint32_t)ap[u] < n) acc[u & 1] = fmaf(cp[u], x[u], acc[u & 1]);
+        }
+        float s = 0.0f;
+        if (hi < n) s = hv * wt[hi];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (ti[u] < n) s = fmaf(tv[u], wt[ti[u]], s);
+        for (te += kVoxelStep; te < e1; te += kVoxelLanes) {   // a tail longer than a step: unequal offsets
+            const uint32_t j = (uint32_t)t_indices[te];
+            if (j < n) s = fmaf(t_values[te], wt[j], s);
+        }
+        s += acc[0] + acc[1];
+#pragma unroll
+        for (int d = kVoxelLanes / 2; d > 0; d >>= 1) s += __shfl_xor(s, d, kWave);
+        if (l == 0) dose[i] = s;
+        if (in >= n_voxels) break;
+        i = in;
+        e0 = n0;
+        e1 = n1;
+    }
 }
 
 /* ------------------------------------------------------------ transpose */
@@ -882,8 +932,13 @@ hipError_t launch_fluence_gradient(const int64_t *indptr, const int32_t *indices
 hipError_t launch_voxel_dose(const int64_t *t_indptr, const int32_t *t_indices, const float *t_values, int n_voxels,
                              int n_w, const float *w, float *dose, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_voxel_dose, dim3(blocks_of((int64_t)n_voxels * 16, kBlock)), dim3(kBlock), 0, s, t_indptr,
-                       t_indices, t_values, n_voxels, n_w, w, dose);
+    const unsigned blocks = std::min(blocks_of((int64_t)n_voxels, kVoxelRows), (unsigned)kVoxelGroups);
+    if (n_w <= kVoxelLdsWords)
+        hipLaunchKernelGGL(k_voxel_dose<true>, dim3(blocks), dim3(kVoxelBlock), sizeof(float) * (size_t)n_w, s,
+                           t_indptr, t_indices, t_values, n_voxels, n_w, w, dose);
+    else
+        hipLaunchKernelGGL(k_voxel_dose<false>, dim3(blocks), dim3(kVoxelBlock), 0, s, t_indptr, t_indices, t_values,
+                           n_voxels, n_w, w, dose);
     return hipGetLastError();
 }
 
