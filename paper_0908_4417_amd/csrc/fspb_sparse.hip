@@ -380,22 +380,34 @@ typedef float vf4 __attribute__((ext_vector_type(4)));
 
 /*
  * g_j = sum_i D_ij r_i; one workgroup per row.  The row's middle goes in steps
- * of 4 kBlock entries: lane l of wave w takes entries 256 w + l + 64 k
+ * of 4 BLOCK entries: lane l of wave w takes entries 256 w + l + 64 k
  * (k < 4) of a step, so that each gather of r reads 64 consecutive columns;
- * the next step's indices and values are loaded (non-temporal: streamed once,
- * kept from displacing r in the caches) after this step's gathers are issued,
- * so they are in flight while the gathered values are awaited.  The tail is
- * lane-strided; lane partial sums, a fixed butterfly per wave and the wave
- * totals added in wave order.  Columns outside [0, n_voxels) are skipped.
+ * the next step's indices and values are loaded after this step's gathers are
+ * issued, so they are in flight while the gathered values are awaited.  The tail
+ * is lane-strided and loaded with the first step; lane partial sums, a fixed
+ * butterfly per wave and the wave totals added in wave order.  Columns outside
+ * [0, n_voxels) are skipped.
+ *
+ * Bound by the read of D.  Rows start anywhere, so steps share cache lines: marked
+ * as streamed the loads fetch them twice (1018 us where these take 947).  Wide
+ * workgroups, so that few rows fill the chip and a row is read in few steps; 512
+ * threads where there are many rows, which are then short (12500 rows of 4300
+ * entries: 82 us, 1024 threads 88; 8100 of 80000: 987 and 947; 240 of them: 41
+ * and 30).
+ * 128^3, 9 beams of 900, 6.5e8 entries: 947 us (5.5 TB/s), with 256 threads and
+ * streamed loads 1070; 128^3, 3 beams of 80: 104 -> 30.
  */
-__global__ __launch_bounds__(kBlock) void k_fluence_gradient(const int64_t *__restrict__ indptr,
-                                                             const int32_t *__restrict__ indices,
-                                                             const float *__restrict__ values, int n_rows,
-                                                             int n_voxels, const float *__restrict__ r,
-                                                             float *__restrict__ g)
+constexpr int kGradRows = 10240;
+template <int BLOCK>
+__global__ __launch_bounds__(BLOCK) void k_fluence_gradient(const int64_t *__restrict__ indptr,
+                                                            const int32_t *__restrict__ indices,
+                                                            const float *__restrict__ values, int n_rows,
+                                                            int n_voxels, const float *__restrict__ r,
+                                                            float *__restrict__ g)
 {
-    constexpr int kStep = 4 * kBlock;
-    __shared__ float s_w[kWavesPerBlock];
+    constexpr int kStep = 4 * BLOCK;
+    constexpr int kWaves = BLOCK / kWave;
+    __shared__ float s_w[kWaves];
     const int j = blockIdx.x;
     const int t = threadIdx.x;
     const uint32_t n = (uint32_t)n_voxels;
@@ -403,15 +415,25 @@ __global__ __launch_bounds__(kBlock) void k_fluence_gradient(const int64_t *__re
     // whole steps from the row's start (4-byte loads need no alignment), then the tail
     const int64_t b = e0 + (e1 - e0) / kStep * kStep;
     float acc0 = 0.0f, acc1 = 0.0f;
-    if (e0 < b) {   // the same for the whole workgroup, as is every step test below
-        int64_t e = e0 + 4 * kWave * (t >> 6) + (t & (kWave - 1));
-        uint32_t i0[4];
-        float v0[4];
+    int64_t e = e0 + 4 * kWave * (t >> 6) + (t & (kWave - 1));
+    uint32_t i0[4], ti[4];
+    float v0[4], tv[4];
+    if (e0 < b) {
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            i0[k] = (uint32_t)__builtin_nontemporal_load(indices + e + kWave * k);
-            v0[k] = __builtin_nontemporal_load(values + e + kWave * k);
+            i0[k] = (uint32_t)indices[e + kWave * k];
+            v0[k] = values[e + kWave * k];
         }
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        ti[k] = ~0u;
+        if (b + t + BLOCK * k < e1) {
+            ti[k] = (uint32_t)indices[b + t + BLOCK * k];
+            tv[k] = values[b + t + BLOCK * k];
+        }
+    }
+    if (e0 < b) {   // the same for the whole workgroup, as is every step test below
         for (;;) {
             const int64_t en = e + kStep;
             float x[4];
@@ -427,8 +449,8 @@ __global__ __launch_bounds__(kBlock) void k_fluence_gradient(const int64_t *__re
             if (en < b) {
 #pragma unroll
                 for (int k = 0; k < 4; ++k) {
-                    i1[k] = (uint32_t)__builtin_nontemporal_load(indices + en + kWave * k);
-                    v1[k] = __builtin_nontemporal_load(values + en + kWave * k);
+                    i1[k] = (uint32_t)indices[en + kWave * k];
+                    v1[k] = values[en + kWave * k];
                 }
             }
 #pragma unroll
@@ -443,16 +465,15 @@ __global__ __launch_bounds__(kBlock) void k_fluence_gradient(const int64_t *__re
             e = en;
         }
     }
-    for (int64_t q = b + t; q < e1; q += kBlock) {
-        const uint32_t i = (uint32_t)indices[q];
-        if (i < n) acc1 = fmaf(values[q], r[i], acc1);
-    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+        if (ti[k] < n) acc1 = fmaf(tv[k], r[ti[k]], acc1);
     const float s = wave_sum(acc0 + acc1);
     if (lane_id() == 0) s_w[t >> 6] = s;
     __syncthreads();
     if (t == 0) {
         float tot = s_w[0];
-        for (int k = 1; k < kWavesPerBlock; ++k) tot += s_w[k];
+        for (int k = 1; k < kWaves; ++k) tot += s_w[k];
         g[j] = tot;
     }
 }
@@ -924,8 +945,12 @@ hipError_t launch_fluence_gradient(const int64_t *indptr, const int32_t *indices
                                    int n_voxels, const float *r, float *g, hipStream_t s)
 {
     if (n_rows == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_fluence_gradient, dim3(n_rows), dim3(kBlock), 0, s, indptr,
-                       indices, values, n_rows, n_voxels, r, g);
+    if (n_rows <= kGradRows)
+        hipLaunchKernelGGL(k_fluence_gradient<1024>, dim3(n_rows), dim3(1024), 0, s, indptr, indices, values, n_rows,
+                           n_voxels, r, g);
+    else
+        hipLaunchKernelGGL(k_fluence_gradient<512>, dim3(n_rows), dim3(512), 0, s, indptr, indices, values, n_rows,
+                           n_voxels, r, g);
     return hipGetLastError();
 }
 
