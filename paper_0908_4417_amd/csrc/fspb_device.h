@@ -135,8 +135,8 @@ struct alignas(16) OutDev {
 
 /* Launchers (fspb_kernels.hip).  Each returns the launch's hipError_t. */
 hipError_t launch_prep(const PlanDev *dplan, const PlanDev &h, hipStream_t s);
-hipError_t launch_raytrace(const PlanDev *dplan, const PlanDev &h, hipStream_t s);
-hipError_t launch_count(const PlanDev *dplan, const PlanDev &h, hipStream_t s);
+/* VOI counts (after the prep stage) and depth tables, either or both in one launch. */
+hipError_t launch_trace(const PlanDev *dplan, const PlanDev &h, bool count, bool depth, hipStream_t s);
 hipError_t launch_scan(const PlanDev *dplan, const OutDev *dout, const PlanDev &h, hipStream_t s);
 /* Fill rows row0 .. row0 + n_rows - 1 (dout->row0 must equal row0). */
 hipError_t launch_fill(const PlanDev *dplan, const OutDev *dout, const PlanDev &h, int row0, int n_rows,

@@ -879,15 +879,17 @@ fspb_status fspb_raytrace(fspb_plan *p, void *stream)
     hipStream_t s = static_cast<hipStream_t>(stream);
     fspb_status us = plan_upload(p, s);
     if (us != FSPB_OK) return us;
-    // the VOI counts need only the mask, so they run before the depth tables: queued behind
-    // another plan's fill, they then get the CUs that fill's last workgroups leave free
+    // the VOI counts and the depth tables need nothing of each other: one launch, the counts first
+    // (their workgroups are the longer ones)
     if (p->timing) FSPB_HIP(hipEventRecord(p->ev[0], s), "record event");
     FSPB_HIP(fspb::launch_prep(p->d_plan, p->h, s), "launch prep");
-    if (p->timing) FSPB_HIP(hipEventRecord(p->ev[1], s), "record event");
-    FSPB_HIP(fspb::launch_count(p->d_plan, p->h, s), "launch count");
-    if (p->timing) FSPB_HIP(hipEventRecord(p->ev[3], s), "record event");
-    FSPB_HIP(fspb::launch_raytrace(p->d_plan, p->h, s), "launch raytrace");
-    if (p->timing) {
+    if (!p->timing) {
+        FSPB_HIP(fspb::launch_trace(p->d_plan, p->h, true, true, s), "launch count and raytrace");
+    } else {   // one after the other, so that each can be timed
+        FSPB_HIP(hipEventRecord(p->ev[1], s), "record event");
+        FSPB_HIP(fspb::launch_trace(p->d_plan, p->h, true, false, s), "launch count");
+        FSPB_HIP(hipEventRecord(p->ev[3], s), "record event");
+        FSPB_HIP(fspb::launch_trace(p->d_plan, p->h, false, true, s), "launch raytrace");
         FSPB_HIP(hipEventRecord(p->ev[2], s), "record event");
         p->have_trace_ev = true;
     }

@@ -3,10 +3,10 @@
  *
  *   k_prep      density mask (one bit per voxel) and per-grid-row extent of
  *               voxels above rho_min                          -- one wave per grid row
- *   k_raytrace  radiological-depth table of every beamlet (Sec. 2.2): Siddon
+ *   k_trace     VOI members per tile of 64 grid rows (Sec. 2.1 VOI rule) and
+ *               per beamlet row                       -- a workgroup or wave per beamlet
+ *               and the radiological-depth table of every beamlet (Sec. 2.2): Siddon
  *               crossings in FP64, compensated FP32 path sums  -- one wave per beamlet
- *   k_count     VOI members per tile of 64 grid rows (Sec. 2.1 VOI rule) and
- *               per beamlet row                                -- one wave per beamlet
  *   k_scan      exclusive scan -> CSR row pointers              -- one workgroup
  *   k_fill      Eq. 2-3 at every VOI voxel, compacted with wave ballots into
  *               ascending CSR columns                          -- one workgroup per beamlet
@@ -255,7 +255,7 @@ __device__ void raytrace_trilinear(const PlanDev &P, const BeamletRec &R, float 
     }
 }
 
-// inlined: as a call it held k_raytrace at 196 VGPRs (two waves per SIMD), inlined it needs 90
+// inlined: as a call it held its kernel at 196 VGPRs (two waves per SIMD), inlined it needs 90
 __device__ __attribute__((always_inline)) inline void raytrace_beamlet(const PlanDev &P, int j)
 {
     const int lane = lane_id();
@@ -283,13 +283,6 @@ __device__ __attribute__((always_inline)) inline void raytrace_beamlet(const Pla
         const cpair last = {__shfl(acc.s, kWave - 1, kWave), __shfl(acc.c, kWave - 1, kWave)};
         carry = cp_add(carry, last);
     }
-}
-
-__global__ __launch_bounds__(kBlock) void k_raytrace(const PlanDev *__restrict__ plans)
-{
-    const PlanDev &P = plans[0];
-    const int j = blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);
-    if (j < P.n_beamlets) raytrace_beamlet(P, j);
 }
 
 /* --------------------------------------------------------- VOI per row */
@@ -496,11 +489,101 @@ __device__ void count_beamlet(const PlanDev &P, int j)
     }
 }
 
-__global__ __launch_bounds__(kBlock) void k_count(const PlanDev *__restrict__ plans)
+/*
+ * count_beamlet with a workgroup per beamlet: a wave takes every kWavesPerBlock-th pair of groups;
+ * the list positions of a step's groups follow from the waves' row counts (LDS), and the list
+ * tiles' members are summed in s_tile (n_tiles integers, any order).
+ */
+__device__ void count_beamlet_wide(const PlanDev &P, int j, int *s_tile)
 {
+    constexpr int W = kWavesPerBlock;
+    __shared__ int s_rows[2][W];
+    __shared__ unsigned long long s_total;
+    const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const BeamletRec &R = P.rec[j];
+    const RowGeom G = row_geom(R);
+    const int c1_pos = __builtin_amdgcn_readfirstlane(R.c1_pos), c1_neg = __builtin_amdgcn_readfirstlane(R.c1_neg);
+    const int n_iy = R.n_iy, iy0 = R.iy0, iz0 = R.iz0, tile0 = R.tile0, n_tiles = R.n_tiles;
+    const int n_rows = n_iy * R.n_iz;
+    const int nx = P.nx, ny = P.ny, wpr = P.wpr;
+    const uint32_t *__restrict__ bits = P.bits;
+    const int2 *__restrict__ ext = P.ext;
+    int32_t *__restrict__ tile_count = P.tile_count;
+    int32_t *__restrict__ list = P.row_list + (int64_t)tile0 * kRowsPerTile;
+    for (int i = threadIdx.x; i < n_tiles; i += W * kWave) s_tile[i] = 0;
+    if (threadIdx.x == 0) s_total = 0;
+    const int r0 = 2 * kRowsPerTile * wave + lane;
+    RowCursor ca{r0 % n_iy, r0 / n_iy};
+    RowCursor cb{(r0 + kRowsPerTile) % n_iy, (r0 + kRowsPerTile) / n_iy};
+    const int dy = (2 * kRowsPerTile * W) % n_iy, dz = (2 * kRowsPerTile * W) / n_iy;
+    int n = 0, total = 0;   // rows in the list before this step (the same in every wave), the wave's members
+    auto append = [&](int x, uint64_t ne, int at, int r) {
+        const int pos = at + mbcnt64(ne);
+        if (x > 0) list[pos] = r;
+        const int incl = wave_incl_scan(x), sum = __builtin_amdgcn_readlane(incl, kWave - 1);
+        const int cnt = __popcll(ne), t0 = at >> 6, room = kRowsPerTile * (t0 + 1) - at;
+        int sa = sum;
+        if (cnt > room) {   // the group starts the next tile
+            const uint64_t last = __ballot(x > 0 && pos == at + room - 1);
+            sa = __builtin_amdgcn_readlane(incl, (int)__builtin_ctzll(last));
+            if (lane == 0) atomicAdd(&s_tile[t0 + 1], sum - sa);
+        }
+        if (lane == 0 && cnt) atomicAdd(&s_tile[t0], sa);
+        return sum;
+    };
+    int buf = 0;
+    for (int t = 2 * wave; t - 2 * wave < n_tiles; t += 2 * W, buf ^= 1) {
+        const int r = t * kRowsPerTile + lane;
+        const int x0 = count_row(G, c1_pos, c1_neg, bits, ext, nx, ny, wpr, iy0, iz0, ca, r < n_rows);
+        const int x1 = count_row(G, c1_pos, c1_neg, bits, ext, nx, ny, wpr, iy0, iz0, cb, r + kRowsPerTile < n_rows);
+        const uint64_t b0 = __ballot(x0 > 0), b1 = __ballot(x1 > 0);
+        if (lane == 0) s_rows[buf][wave] = __popcll(b0) + __popcll(b1);
+        __syncthreads();
+        const int before = wave_incl_scan(lane < W ? s_rows[buf][lane] : 0);
+        const int at = n + (wave ? __builtin_amdgcn_readlane(before, max(wave - 1, 0)) : 0);
+        n += __builtin_amdgcn_readlane(before, W - 1);
+        const int c0 = append(x0, b0, at, r), c1 = append(x1, b1, at + __popcll(b0), r + kRowsPerTile);
+        if (lane == 0) {
+            if (t < n_tiles) tile_count[tile0 + t] = c0;
+            if (t + 1 < n_tiles) tile_count[tile0 + t + 1] = c1;
+        }
+        total += c0 + c1;
+        ca.step(dy, dz, n_iy);
+        cb.step(dy, dz, n_iy);
+    }
+    __syncthreads();   // also where there is no tile: s_total is set
+    if (lane == 0) atomicAdd(&s_total, (unsigned long long)total);
+    for (int i = threadIdx.x; i < (n + kRowsPerTile - 1) / kRowsPerTile; i += W * kWave) P.list_count[tile0 + i] = s_tile[i];
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        P.row_nnz[j] = (int64_t)s_total;
+        const bool rows = P.tiles_mode == 0 ? 2 * n < n_rows : P.tiles_mode == 2;
+        P.row_ne[j] = rows ? n : -1;
+    }
+}
+
+/*
+ * VOI counts and depth tables, which need nothing of each other, in one launch: the workgroups
+ * below n_count count (WIDE: a beamlet each, else one per wave), the others trace a beamlet per
+ * wave.  Both are chains of latency (grid rows in steps of 128, crossings in FP64) and together
+ * hide each other's: 64^3 plan of 100 beamlets 59 -> 41 us (one wave per count, a launch each: 20
+ * and 10 us of it), 9 x 576 on 256x256x100 1355 -> 1335.
+ */
+template <bool WIDE>
+__global__ __launch_bounds__(kBlock) void k_trace(const PlanDev *__restrict__ plans, int n_count)
+{
+    extern __shared__ int s_tile[];
     const PlanDev &P = plans[0];
-    const int j = blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);
-    if (j < P.n_beamlets) count_beamlet(P, j);
+    const int wave = threadIdx.x >> 6;
+    if ((int)blockIdx.x >= n_count) {
+        const int j = ((int)blockIdx.x - n_count) * kWavesPerBlock + wave;
+        if (j < P.n_beamlets) raytrace_beamlet(P, j);
+    } else if (WIDE) {
+        count_beamlet_wide(P, (int)blockIdx.x, s_tile);
+    } else {
+        const int j = (int)blockIdx.x * kWavesPerBlock + wave;
+        if (j < P.n_beamlets) count_beamlet(P, j);
+    }
 }
 
 /* ---------------------------------------------------------------- scan */
@@ -1414,17 +1497,23 @@ hipError_t launch_prep(const PlanDev *dplan, const PlanDev &h, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_raytrace(const PlanDev *dplan, const PlanDev &h, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_raytrace, dim3(blocks_for(h.n_beamlets, kWavesPerBlock)), dim3(kBlock), 0, s,
-                       dplan);
-    return hipGetLastError();
-}
+// A workgroup per beamlet where one wave per beamlet leaves wave slots of the 1024 SIMDs empty
+// (715 beamlets: plan 191 us, one wave each 215; 12500: 398 and 381), within 32 KB of tile sums.
+constexpr int kCountWide = 8192;
+constexpr int kCountTiles = 8192;
 
-hipError_t launch_count(const PlanDev *dplan, const PlanDev &h, hipStream_t s)
+hipError_t launch_trace(const PlanDev *dplan, const PlanDev &h, bool count, bool depth, hipStream_t s)
 {
     if (h.n_beamlets == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_count, dim3(blocks_for(h.n_beamlets, kWavesPerBlock)), dim3(kBlock), 0, s, dplan);
+    const bool wide = h.n_beamlets <= kCountWide && h.max_tiles <= kCountTiles;
+    const unsigned waves = blocks_for(h.n_beamlets, kWavesPerBlock);
+    const unsigned n_count = !count ? 0 : wide ? (unsigned)h.n_beamlets : waves;
+    const dim3 grid(n_count + (depth ? waves : 0));
+    if (wide)
+        hipLaunchKernelGGL(k_trace<true>, grid, dim3(kBlock), sizeof(int) * (size_t)h.max_tiles, s, dplan,
+                           (int)n_count);
+    else
+        hipLaunchKernelGGL(k_trace<false>, grid, dim3(kBlock), 0, s, dplan, (int)n_count);
     return hipGetLastError();
 }
 
