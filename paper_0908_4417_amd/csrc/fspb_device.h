@@ -137,10 +137,10 @@ struct alignas(16) OutDev {
 hipError_t launch_prep(const PlanDev *dplan, const PlanDev &h, hipStream_t s);
 /* VOI counts (after the prep stage) and depth tables, either or both in one launch. */
 hipError_t launch_trace(const PlanDev *dplan, const PlanDev &h, bool count, bool depth, hipStream_t s);
-hipError_t launch_scan(const PlanDev *dplan, const OutDev *dout, const PlanDev &h, hipStream_t s);
-/* Fill rows row0 .. row0 + n_rows - 1 (dout->row0 must equal row0). */
-hipError_t launch_fill(const PlanDev *dplan, const OutDev *dout, const PlanDev &h, int row0, int n_rows,
-                       hipStream_t s);
+/* Row pointers and the nonzero count, which is also written to nnz_host (pinned). */
+hipError_t launch_scan(const PlanDev *dplan, int64_t *indptr, int64_t *nnz_host, hipStream_t s);
+/* Fill rows out.row0 .. out.row0 + n_rows - 1. */
+hipError_t launch_fill(const PlanDev *dplan, const OutDev &out, const PlanDev &h, int n_rows, hipStream_t s);
 /* LDS of one fill workgroup (the erf table and the dynamic part): in the form launch_fill uses, or in
  * a given erf table form; and the dynamic part alone. */
 size_t fill_dynamic_bytes(const PlanDev &h);

@@ -76,7 +76,7 @@ size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
  * writes come first, so that one copy of [0, upload) uploads all of them. */
 struct Layout {
     size_t plan, scal, rec, pdd, erf, ctab, atab, upload;
-    size_t out, tile_count, row_list, list_count, row_ne, row_nnz, tables, bits, ext, total;
+    size_t tile_count, row_list, list_count, row_ne, row_nnz, tables, bits, ext, total;
 };
 
 /*
@@ -117,12 +117,11 @@ void stage_release(Staging *b)
 const std::vector<float2> &fill_erf_table();
 
 /*
- * Pinned 64-byte host slots, one per plan, that a plan's nonzero count is
- * copied back into: an asynchronous copy into pinned memory lets
- * fspb_dose_coeffs queue the fill before it waits for the count; and one per
- * surrogate, that a gradient's kernel writes its loss to.  Slots are
- * carved from pinned pages and recycled; the pages are kept until the process
- * ends.
+ * Pinned 64-byte host slots, one per plan, that the scan writes a plan's
+ * nonzero count to, so that fspb_dose_coeffs queues the fill before it waits
+ * for the count; and one per surrogate, that a gradient's kernel writes its
+ * loss to.  Slots are carved from pinned pages and recycled; the pages are kept
+ * until the process ends.
  */
 std::mutex g_slot_mu;
 std::vector<void *> g_slot_pages;
@@ -154,9 +153,8 @@ void slot_release(int64_t *slot)
 
 struct fspb_plan {
     PlanDev h{};                  // host image of the device record (device pointers inside)
-    OutDev out{};                 // host image of the output record
+    OutDev out{};                 // the output record fills are launched with
     PlanDev *d_plan = nullptr;
-    OutDev *d_out = nullptr;
     int64_t *d_nnz = nullptr;
     int32_t *d_overflow = nullptr;
     std::vector<BeamletRec> recs;
@@ -175,8 +173,8 @@ struct fspb_plan {
     Staging *upload = nullptr;          // claimed staging buffer of a pending upload
     size_t upload_bytes = 0;            // its length: workspace bytes [0, upload_bytes)
     int32_t batches = 0;                // live batches holding this plan
-    int64_t *nnz_host = nullptr;        // pinned slot the nonzero count is read into
-    hipEvent_t nnz_ready = nullptr;     // recorded after that read
+    int64_t *nnz_host = nullptr;        // pinned slot the scan writes the nonzero count to
+    hipEvent_t nnz_ready = nullptr;     // recorded after the scan
     ~fspb_plan()
     {
         for (hipEvent_t &e : ev)
@@ -774,7 +772,6 @@ fspb_status fspb_plan_create(const fspb_grid *g, const fspb_beam *beams, int32_t
         L.atab = take(sizeof(float) * (size_t)K->tables->n_theta * K->tables->n_adepth);
     }
     L.upload = off;
-    L.out = take(sizeof(OutDev));
     L.tile_count = take(sizeof(int32_t) * (size_t)std::max<int64_t>(tile_off, 1));
     L.row_list = take(sizeof(int32_t) * (size_t)std::max<int64_t>(tile_off * fspb::kRowsPerTile, 1));
     L.list_count = take(sizeof(int32_t) * (size_t)std::max<int64_t>(tile_off, 1));
@@ -805,7 +802,6 @@ fspb_status fspb_plan_create(const fspb_grid *g, const fspb_beam *beams, int32_t
 
     char *ws = static_cast<char *>(workspace);
     p->d_plan = reinterpret_cast<PlanDev *>(ws + L.plan);
-    p->d_out = reinterpret_cast<OutDev *>(ws + L.out);
     p->d_nnz = reinterpret_cast<int64_t *>(ws + L.scal);
     p->d_overflow = reinterpret_cast<int32_t *>(ws + L.scal + 16);
     h.rec = reinterpret_cast<BeamletRec *>(ws + L.rec);
@@ -916,19 +912,17 @@ fspb_status fspb_dose_coeffs(fspb_plan *p, int64_t *indptr, int32_t *indices, fl
     p->out.row0 = 0;
     p->out.check_nnz = 1;
     p->counted = false;
-    FSPB_HIP(hipMemcpyAsync(p->d_out, &p->out, sizeof(OutDev), hipMemcpyHostToDevice, s), "upload output record");
     p->have_dose_ev = false;
     // tile and row counts were made by fspb_raytrace
     if (p->timing) FSPB_HIP(hipEventRecord(p->ev[4], s), "record event");
-    FSPB_HIP(fspb::launch_scan(p->d_plan, p->d_out, p->h, s), "launch scan");
+    FSPB_HIP(fspb::launch_scan(p->d_plan, indptr, p->nnz_host, s), "launch scan");
     if (p->timing) FSPB_HIP(hipEventRecord(p->ev[5], s), "record event");
-    FSPB_HIP(hipMemcpyAsync(p->nnz_host, p->d_nnz, sizeof(int64_t), hipMemcpyDeviceToHost, s), "read nnz");
     FSPB_HIP(hipEventRecord(p->nnz_ready, s), "record count event");
     // the fill is queued before the count is known; it writes nothing unless the total fits
     const bool fill = indices && values && capacity > 0;
     if (fill) {
         if (p->timing) FSPB_HIP(hipEventRecord(p->ev[6], s), "record event");
-        FSPB_HIP(fspb::launch_fill(p->d_plan, p->d_out, p->h, 0, p->h.n_beamlets, s), "launch fill");
+        FSPB_HIP(fspb::launch_fill(p->d_plan, p->out, p->h, p->h.n_beamlets, s), "launch fill");
         if (p->timing) FSPB_HIP(hipEventRecord(p->ev[7], s), "record event");
     }
     FSPB_HIP(hipEventSynchronize(p->nnz_ready), "wait for nnz");
@@ -970,8 +964,7 @@ fspb_status fspb_dose_coeffs_rows(fspb_plan *p, int32_t j0, int32_t j1, const in
     p->out.overflow = p->d_overflow;
     p->out.row0 = j0;
     p->out.check_nnz = 0;   // the range's size was checked above
-    FSPB_HIP(hipMemcpyAsync(p->d_out, &p->out, sizeof(OutDev), hipMemcpyHostToDevice, s), "upload output record");
-    FSPB_HIP(fspb::launch_fill(p->d_plan, p->d_out, p->h, j0, j1 - j0, s), "launch fill");
+    FSPB_HIP(fspb::launch_fill(p->d_plan, p->out, p->h, j1 - j0, s), "launch fill");
     return FSPB_OK;
 }
 

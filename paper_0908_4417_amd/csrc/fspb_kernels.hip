@@ -77,9 +77,6 @@ __device__ inline int wave_incl_scan(int x)
     return x;
 }
 
-/* Wave total of 32-bit integers (every lane active), the same on every lane. */
-__device__ inline int wave_sum(int x) { return __builtin_amdgcn_readlane(wave_incl_scan(x), kWave - 1); }
-
 /* ---------------------------------------------------------------- prep */
 
 /* Mask bits and member extent of grid row `row` (= iz * ny + iy); one wave. */
@@ -590,8 +587,9 @@ __global__ __launch_bounds__(kBlock) void k_trace(const PlanDev *__restrict__ pl
 
 constexpr int kScanBlock = 1024;
 
-/* Exclusive scan of row_nnz into indptr[0..n]; indptr[n] = nnz.  One workgroup of kScanBlock. */
-__device__ void scan_plan(const PlanDev &P, int64_t *indptr)
+/* Exclusive scan of row_nnz into indptr[0..n]; indptr[n] = nnz, also stored to
+ * nnz_host (pinned) if given, so that no copy has to follow.  One workgroup of kScanBlock. */
+__device__ void scan_plan(const PlanDev &P, int64_t *indptr, int64_t *nnz_host = nullptr)
 {
     // each thread takes kScanPer consecutive rows per pass, so one pass covers 8192 rows and
     // all of its loads are issued together
@@ -630,13 +628,14 @@ __device__ void scan_plan(const PlanDev &P, int64_t *indptr)
     if (tid == 0) {
         indptr[n] = carry_s;
         P.nnz[0] = carry_s;
+        if (nnz_host) __hip_atomic_store(nnz_host, carry_s, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
     }
 }
 
 __global__ __launch_bounds__(kScanBlock) void k_scan(const PlanDev *__restrict__ plans,
-                                                      const OutDev *__restrict__ outs)
+                                                      int64_t *__restrict__ indptr, int64_t *nnz_host)
 {
-    scan_plan(plans[0], outs[0].indptr);
+    scan_plan(plans[0], indptr, nnz_host);
 }
 
 /* ---------------------------------------------------------------- fill */
@@ -1389,13 +1388,13 @@ __device__ __attribute__((always_inline)) inline void fill_beamlet(const PlanDev
 // surrogate's: two, so that at most 256 registers are used and none lies in the accumulation file
 template <int K, bool SURR, bool GEN, int EM>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(SURR ? 2 : GEN || K > 2 ? 1 : 6))) void k_fill(const PlanDev *__restrict__ plans,
-                                                  const OutDev *__restrict__ outs)
+                                                  const OutDev out)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ __align__(16) float2 s_erf[erf_pairs(EM)];   // at a fixed address: see erf_diff
     // launched before the host has read the plan's total: write nothing if it does not fit
-    if (outs[0].check_nnz && *plans[0].nnz > outs[0].capacity) return;
-    fill_beamlet<K, kWavesPerBlock, false, SURR, GEN, EM>(plans[0], outs[0], outs[0].row0 + (int)blockIdx.x, s_erf, smem, 1,
+    if (out.check_nnz && *plans[0].nnz > out.capacity) return;
+    fill_beamlet<K, kWavesPerBlock, false, SURR, GEN, EM>(plans[0], out, out.row0 + (int)blockIdx.x, s_erf, smem, 1,
                                                          (int)blockIdx.y, (int)gridDim.y);
 }
 
@@ -1517,9 +1516,9 @@ hipError_t launch_trace(const PlanDev *dplan, const PlanDev &h, bool count, bool
     return hipGetLastError();
 }
 
-hipError_t launch_scan(const PlanDev *dplan, const OutDev *dout, const PlanDev &h, hipStream_t s)
+hipError_t launch_scan(const PlanDev *dplan, int64_t *indptr, int64_t *nnz_host, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_scan, dim3(1), dim3(kScanBlock), 0, s, dplan, dout);
+    hipLaunchKernelGGL(k_scan, dim3(1), dim3(kScanBlock), 0, s, dplan, indptr, nnz_host);
     return hipGetLastError();
 }
 
@@ -1690,25 +1689,23 @@ static unsigned fill_parts(const PlanDev &h, int n_rows)
     return (unsigned)std::min(most, std::max(1, (kFillGroups + n_rows - 1) / n_rows));
 }
 
-hipError_t launch_fill(const PlanDev *dplan, const OutDev *dout, const PlanDev &h, int row0, int n_rows,
-                       hipStream_t s)
+hipError_t launch_fill(const PlanDev *dplan, const OutDev &out, const PlanDev &h, int n_rows, hipStream_t s)
 {
-    (void)row0;   // read by the kernel from the output record
     if (n_rows <= 0) return hipSuccess;
     const dim3 grid(n_rows, fill_parts(h, n_rows)), block(kBlock);
     const size_t lds = fill_dynamic_bytes(h);
     if (h.use_mlp) {
         switch (h.n_terms) {
-        case 1: hipLaunchKernelGGL((k_fill<1, true, false, 0>), grid, block, lds, s, dplan, dout); break;
-        case 2: hipLaunchKernelGGL((k_fill<2, true, false, 0>), grid, block, lds, s, dplan, dout); break;
-        case 3: hipLaunchKernelGGL((k_fill<3, true, false, 0>), grid, block, lds, s, dplan, dout); break;
-        default: hipLaunchKernelGGL((k_fill<4, true, false, 0>), grid, block, lds, s, dplan, dout); break;
+        case 1: hipLaunchKernelGGL((k_fill<1, true, false, 0>), grid, block, lds, s, dplan, out); break;
+        case 2: hipLaunchKernelGGL((k_fill<2, true, false, 0>), grid, block, lds, s, dplan, out); break;
+        case 3: hipLaunchKernelGGL((k_fill<3, true, false, 0>), grid, block, lds, s, dplan, out); break;
+        default: hipLaunchKernelGGL((k_fill<4, true, false, 0>), grid, block, lds, s, dplan, out); break;
         }
         return hipGetLastError();
     }
     const int em = h.erf_mode;
     const void *f = h.gen ? fill_kernel_ptr<true>(h.n_terms, em) : fill_kernel_ptr<false>(h.n_terms, em);
-    void *args[] = {const_cast<PlanDev **>(&dplan), const_cast<OutDev **>(&dout)};
+    void *args[] = {const_cast<PlanDev **>(&dplan), const_cast<OutDev *>(&out)};
     return hipLaunchKernel(f, grid, block, args, lds, s);
 }
 

@@ -332,7 +332,7 @@ __global__ __launch_bounds__(kReduceParams *kReduceWaves) void k_mlp_reduce(
         }
     }
     if (!last || !mine) return;
-    if (k == kMlpParams && loss_out) *loss_out = gsum;
+    if (k == kMlpParams && loss_out) __hip_atomic_store(loss_out, gsum, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
     else if (grad_out) grad_out[k] = gsum;
     if (!update) return;
     const float mm = fmaf(1.0f - b1, gsum, b1 * o1);
