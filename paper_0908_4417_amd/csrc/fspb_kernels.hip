@@ -79,23 +79,38 @@ __device__ inline int wave_incl_scan(int x)
 
 /* ---------------------------------------------------------------- prep */
 
-/* Mask bits and member extent of grid row `row` (= iz * ny + iy); one wave. */
+/*
+ * Mask bits and member extent of grid row `row` (= iz * ny + iy); one wave.  Four loads of 64
+ * voxels are issued together: a row is a chain of them otherwise (a batch of eight
+ * plans 1176 us, 1138 with them together).
+ */
 __device__ void prep_row(const PlanDev &P, int row)
 {
-    const int lane = lane_id();
-    const float *d = P.density + (size_t)row * P.nx;
-    uint32_t *bits = P.bits + (size_t)row * P.wpr;
-    int first = P.nx, last = -1, members = 0;
-    for (int x0 = 0; x0 < P.nx; x0 += kWave) {
-        const int x = x0 + lane;
-        const bool m = x < P.nx && d[x] > P.rho_min;
-        const uint64_t b = __ballot(m);
-        const int w = (x0 >> 5) + lane;
-        if (lane < 2 && w < P.wpr) bits[w] = lane ? (uint32_t)(b >> 32) : (uint32_t)b;
-        if (b) {
-            first = min(first, x0 + __ffsll((unsigned long long)b) - 1);
-            last = x0 + 63 - __clzll((long long)b);
-            members += __popcll(b);
+    constexpr int kAhead = 4;
+    const int lane = lane_id(), nx = P.nx, wpr = P.wpr;
+    const float rho_min = P.rho_min;
+    const float *__restrict__ d = P.density + (size_t)row * nx;
+    uint32_t *__restrict__ bits = P.bits + (size_t)row * wpr;
+    int first = nx, last = -1, members = 0;
+    for (int x0 = 0; x0 < nx; x0 += kAhead * kWave) {
+        float v[kAhead];
+#pragma unroll
+        for (int k = 0; k < kAhead; ++k) {
+            const int x = x0 + k * kWave + lane;
+            v[k] = x < nx ? d[x] : rho_min;
+        }
+#pragma unroll
+        for (int k = 0; k < kAhead; ++k) {
+            const int xk = x0 + k * kWave;
+            if (xk >= nx) break;
+            const uint64_t b = __ballot(v[k] > rho_min);
+            const int w = (xk >> 5) + lane;
+            if (lane < 2 && w < wpr) bits[w] = lane ? (uint32_t)(b >> 32) : (uint32_t)b;
+            if (b) {
+                first = min(first, xk + __ffsll((unsigned long long)b) - 1);
+                last = xk + 63 - __clzll((long long)b);
+                members += __popcll(b);
+            }
         }
     }
     // first > last: no member voxel; kExtHoles marks a row with non-members between them
