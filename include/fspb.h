@@ -190,7 +190,8 @@ typedef struct {
                                     2 mirrored, the first argument of each bracket unclamped
                                     (the plan's widest beamlet over its narrowest sigma keeps
                                     it inside the table); 3 as 2 with square beamlets and a
-                                    non-negative kernel, no argument clamped */
+                                    non-negative kernel, no argument clamped (with or
+                                    without the sigmas of the terms in constant ratios) */
 } fspb_plan_desc;
 
 /*
@@ -494,9 +495,9 @@ void fspb_surrogate_destroy(fspb_surrogate *sur);
 
 /*
  * dose[i] = sum_j w[j] D_ij.  indptr (n_rows + 1), indices, values, w (n_rows)
- * and dose (n_voxels) are DEVICE pointers; dose is overwritten.  Entries are
- * added with FP32 atomics, so the rounding of each voxel's sum depends on
- * the order in which rows land (the value itself is the same to FP32
+ * and dose (n_voxels) are DEVICE pointers; dose is overwritten.  Neighbouring
+ * rows are summed together and the sums added with FP32 atomics, so the
+ * rounding of each voxel's sum depends on the order in which they land (the value itself is the same to FP32
  * precision; fspb_voxel_dose is the bit-reproducible form).  Entries whose
  * column lies outside [0, n_voxels) are skipped.  indices and values are
  * read only where indptr says there are entries (they may be NULL for a
@@ -508,7 +509,7 @@ fspb_status fspb_fluence_dose(const int64_t *indptr, const int32_t *indices, con
 /*
  * g[j] = sum_i D_ij r[i] (the gradient of sum_i r_i D_i with respect to the
  * beamlet weights).  DEVICE pointers; r has n_voxels entries, g has n_rows
- * and is overwritten.  Each row is summed by one wave in a fixed order:
+ * and is overwritten.  Each row is summed by one workgroup in a fixed order:
  * deterministic.  Entries whose column lies outside [0, n_voxels) are skipped;
  * indices and values may be NULL for a matrix without entries.
  */
