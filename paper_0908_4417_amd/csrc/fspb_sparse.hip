@@ -398,6 +398,7 @@ typedef float vf4 __attribute__((ext_vector_type(4)));
  * streamed loads 1070; 128^3, 3 beams of 80: 104 -> 30.
  */
 constexpr int kGradRows = 10240;
+constexpr uint32_t kGradGrid = 0xffffffffu;        // a launch's threads are counted in 32 bits
 template <int BLOCK>
 __global__ __launch_bounds__(BLOCK) void k_fluence_gradient(const int64_t *__restrict__ indptr,
                                                             const int32_t *__restrict__ indices,
@@ -948,8 +949,11 @@ hipError_t launch_fluence_gradient(const int64_t *indptr, const int32_t *indices
     if (n_rows <= kGradRows)
         hipLaunchKernelGGL(k_fluence_gradient<1024>, dim3(n_rows), dim3(1024), 0, s, indptr, indices, values, n_rows,
                            n_voxels, r, g);
-    else
+    else if (n_rows <= kGradGrid / 512)
         hipLaunchKernelGGL(k_fluence_gradient<512>, dim3(n_rows), dim3(512), 0, s, indptr, indices, values, n_rows,
+                           n_voxels, r, g);
+    else
+        hipLaunchKernelGGL(k_fluence_gradient<256>, dim3(n_rows), dim3(256), 0, s, indptr, indices, values, n_rows,
                            n_voxels, r, g);
     return hipGetLastError();
 }
