@@ -54,6 +54,16 @@ constexpr int kScanTop = 1024;
 
 static_assert(kRadix == kBlock && kRadix <= kSortBlock, "one thread per digit");
 
+/* Item of workgroup blockIdx.x where each XCD is to take GROUP consecutive items: workgroups are handed
+ * to the 8 XCDs in turn. */
+constexpr int kXcds = 8;
+template <int GROUP>
+__device__ inline int xcd_item()
+{
+    const int x = (int)(blockIdx.x % kXcds), k = (int)(blockIdx.x / kXcds);
+    return ((k / GROUP) * kXcds + x) * GROUP + k % GROUP;
+}
+
 __device__ inline int lane_id() { return threadIdx.x & (kWave - 1); }
 
 __device__ inline int mbcnt64(uint64_t m)
@@ -380,86 +390,107 @@ typedef float vf4 __attribute__((ext_vector_type(4)));
 
 /*
  * g_j = sum_i D_ij r_i; one workgroup per row.  The row's middle goes in steps
- * of 4 BLOCK entries: lane l of wave w takes entries 256 w + l + 64 k
- * (k < 4) of a step, so that each gather of r reads 64 consecutive columns;
+ * of PER BLOCK entries: lane l of wave w takes entries 64 PER w + l + 64 k
+ * (k < PER) of a step, so that each gather of r reads 64 consecutive columns;
  * the next step's indices and values are loaded after this step's gathers are
  * issued, so they are in flight while the gathered values are awaited.  The tail
- * is lane-strided and loaded with the first step; lane partial sums, a fixed
- * butterfly per wave and the wave totals added in wave order.  Columns outside
- * [0, n_voxels) are skipped.
+ * is lane-strided, four entries of a lane at a time and the first four loaded with the first
+ * step; lane partial sums, a fixed butterfly per wave and the wave totals added in
+ * wave order.  Columns outside [0, n_voxels) are skipped.
  *
  * Bound by the read of D.  Rows start anywhere, so steps share cache lines: marked
- * as streamed the loads fetch them twice (1018 us where these take 947).  Wide
- * workgroups, so that few rows fill the chip and a row is read in few steps; 512
- * threads where there are many rows, which are then short (12500 rows of 4300
- * entries: 82 us, 1024 threads 88; 8100 of 80000: 987 and 947; 240 of them: 41
- * and 30).
- * 128^3, 9 beams of 900, 6.5e8 entries: 947 us (5.5 TB/s), with 256 threads and
- * streamed loads 1070; 128^3, 3 beams of 80: 104 -> 30.
+ * as streamed the loads fetch them twice (128^3, 9 beams of 900, 8.1e4 entries a
+ * row: 1027 us against 977).
+ *
+ * The width follows the number of rows, all that the host knows of the matrix.  Few
+ * rows get 1024 threads each, or most of the chip idles (240 rows of 8e4 entries:
+ * 33 us, 88 with 256).  Many rows may be short, and then what counts is how many
+ * waves have to be launched: 256 threads (9000 rows of 50 entries: 7.6 us, 20.5 with
+ * 1024; of 1000: 18.1 and 31.6; at 2000 rows of 50 the widths are equal, at 4000
+ * they take 7.8 and 10.2).  Long rows then need many entries in flight per lane, or
+ * so many rows are open at once that r falls out of the L2: PER 8 takes 977 us on
+ * that slab, PER 4 999, 1024 threads 948; above kGradMany rows, where rows are
+ * shorter still, PER 4 (40000 of 2000: 119 us, PER 8 131).
+ *
+ * With 256 threads kGradXcd consecutive rows go to one XCD (workgroups are dealt to
+ * the XCDs in turn), since neighbouring beamlets gather the same voxels of r: 977 us
+ * on the slab, 1047 with the rows dealt one by one; groups of 64 take 960 there but
+ * 642 against 626 on 256x256x100 with 9 beams of 576, of 256 994 and 699.
  */
-constexpr int kGradRows = 10240;
-constexpr uint32_t kGradGrid = 0xffffffffu;        // a launch's threads are counted in 32 bits
-template <int BLOCK>
+constexpr int kGradFew = 2048;
+constexpr int kGradMany = 32768;
+constexpr int kGradXcd = 16;
+template <int GROUP>
+__device__ inline int grad_row(int n_rows)
+{
+    const int b = blockIdx.x;
+    if constexpr (GROUP == 0) return b;
+    else return b < n_rows - n_rows % (kXcds * GROUP) ? xcd_item<GROUP>() : b;   // the last, partial set: one by one
+}
+template <int BLOCK, int PER, int GROUP>
 __global__ __launch_bounds__(BLOCK) void k_fluence_gradient(const int64_t *__restrict__ indptr,
                                                             const int32_t *__restrict__ indices,
                                                             const float *__restrict__ values, int n_rows,
                                                             int n_voxels, const float *__restrict__ r,
                                                             float *__restrict__ g)
 {
-    constexpr int kStep = 4 * BLOCK;
+    constexpr int kStep = PER * BLOCK;
     constexpr int kWaves = BLOCK / kWave;
     __shared__ float s_w[kWaves];
-    const int j = blockIdx.x;
+    const int j = grad_row<GROUP>(n_rows);
     const int t = threadIdx.x;
     const uint32_t n = (uint32_t)n_voxels;
     const int64_t e0 = indptr[j], e1 = indptr[j + 1];
     // whole steps from the row's start (4-byte loads need no alignment), then the tail
     const int64_t b = e0 + (e1 - e0) / kStep * kStep;
     float acc0 = 0.0f, acc1 = 0.0f;
-    int64_t e = e0 + 4 * kWave * (t >> 6) + (t & (kWave - 1));
-    uint32_t i0[4], ti[4];
-    float v0[4], tv[4];
+    int64_t e = e0 + PER * kWave * (t >> 6) + (t & (kWave - 1));
+    uint32_t i0[PER], ti[4];
+    float v0[PER], tv[4];
     if (e0 < b) {
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
+        for (int k = 0; k < PER; ++k) {
             i0[k] = (uint32_t)indices[e + kWave * k];
             v0[k] = values[e + kWave * k];
         }
     }
+    auto load_tail = [&](int64_t at) {
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        ti[k] = ~0u;
-        if (b + t + BLOCK * k < e1) {
-            ti[k] = (uint32_t)indices[b + t + BLOCK * k];
-            tv[k] = values[b + t + BLOCK * k];
+        for (int k = 0; k < 4; ++k) {
+            ti[k] = ~0u;
+            if (at + t + BLOCK * k < e1) {
+                ti[k] = (uint32_t)indices[at + t + BLOCK * k];
+                tv[k] = values[at + t + BLOCK * k];
+            }
         }
-    }
+    };
+    load_tail(b);
     if (e0 < b) {   // the same for the whole workgroup, as is every step test below
         for (;;) {
             const int64_t en = e + kStep;
-            float x[4];
+            float x[PER];
 #pragma unroll
-            for (int k = 0; k < 4; ++k) x[k] = i0[k] < n ? r[i0[k]] : 0.0f;
-            uint32_t i1[4];
-            float v1[4];
+            for (int k = 0; k < PER; ++k) x[k] = i0[k] < n ? r[i0[k]] : 0.0f;
+            uint32_t i1[PER];
+            float v1[PER];
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
+            for (int k = 0; k < PER; ++k) {
                 i1[k] = i0[k];
                 v1[k] = v0[k];
             }
             if (en < b) {
 #pragma unroll
-                for (int k = 0; k < 4; ++k) {
+                for (int k = 0; k < PER; ++k) {
                     i1[k] = (uint32_t)indices[en + kWave * k];
                     v1[k] = values[en + kWave * k];
                 }
             }
 #pragma unroll
-            for (int k = 0; k < 4; ++k)
+            for (int k = 0; k < PER; ++k)
                 if (i0[k] < n) acc0 = fmaf(v0[k], x[k], acc0);
             if (en >= b) break;
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
+            for (int k = 0; k < PER; ++k) {
                 i0[k] = i1[k];
                 v0[k] = v1[k];
             }
@@ -467,8 +498,13 @@ __global__ __launch_bounds__(BLOCK) void k_fluence_gradient(const int64_t *__res
         }
     }
 #pragma unroll
-    for (int k = 0; k < 4; ++k)
-        if (ti[k] < n) acc1 = fmaf(tv[k], r[ti[k]], acc1);
+    for (int q = 0; q < PER; q += 4) {
+        if (q && b + BLOCK * q >= e1) break;
+        if (q) load_tail(b + BLOCK * q);
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (ti[k] < n) acc1 = fmaf(tv[k], r[ti[k]], acc1);
+    }
     const float s = wave_sum(acc0 + acc1);
     if (lane_id() == 0) s_w[t >> 6] = s;
     __syncthreads();
@@ -946,15 +982,15 @@ hipError_t launch_fluence_gradient(const int64_t *indptr, const int32_t *indices
                                    int n_voxels, const float *r, float *g, hipStream_t s)
 {
     if (n_rows == 0) return hipSuccess;
-    if (n_rows <= kGradRows)
-        hipLaunchKernelGGL(k_fluence_gradient<1024>, dim3(n_rows), dim3(1024), 0, s, indptr, indices, values, n_rows,
-                           n_voxels, r, g);
-    else if (n_rows <= kGradGrid / 512)
-        hipLaunchKernelGGL(k_fluence_gradient<512>, dim3(n_rows), dim3(512), 0, s, indptr, indices, values, n_rows,
-                           n_voxels, r, g);
+    if (n_rows <= kGradFew)
+        hipLaunchKernelGGL((k_fluence_gradient<1024, 4, 0>), dim3(n_rows), dim3(1024), 0, s, indptr, indices, values,
+                           n_rows, n_voxels, r, g);
+    else if (n_rows <= kGradMany)
+        hipLaunchKernelGGL((k_fluence_gradient<256, 8, kGradXcd>), dim3(n_rows), dim3(256), 0, s, indptr, indices,
+                           values, n_rows, n_voxels, r, g);
     else
-        hipLaunchKernelGGL(k_fluence_gradient<256>, dim3(n_rows), dim3(256), 0, s, indptr, indices, values, n_rows,
-                           n_voxels, r, g);
+        hipLaunchKernelGGL((k_fluence_gradient<256, 4, kGradXcd>), dim3(n_rows), dim3(256), 0, s, indptr, indices,
+                           values, n_rows, n_voxels, r, g);
     return hipGetLastError();
 }
 
@@ -994,7 +1030,6 @@ constexpr int kBucketShift = 5;
 constexpr int kBucketCols = 1 << kBucketShift;
 constexpr uint32_t kRunFlag = 0x80000000u;   // run of invalid columns (in the run's row id)
 constexpr int kRowChunks = 4;                // chunks of 64 entries whose loads are in flight together
-constexpr int kXcds = 8;                     // workgroups are handed to the 8 XCDs in turn
 
 /* Value of the lane below, through a whole-wave DPP shift; lane 0 takes `edge`. */
 __device__ inline int from_lane_below(int v, int edge) { return __builtin_amdgcn_update_dpp(edge, v, 0x138, 0xf, 0xf, false); }
@@ -1205,17 +1240,10 @@ __global__ __launch_bounds__(kBlock) void k_bucket_bounds(const Run *__restrict_
     b_ptr[b] = lo;
 }
 
-/* Bucket handled by workgroup blockIdx.x: groups of kXcdGroup consecutive
- * buckets go to one XCD (workgroups are dealt to the XCDs in turn), so that
- * the runs of neighbouring buckets, which share cache lines of a row, meet in
- * one L2; the groups themselves are dealt to the XCDs in turn, which keeps the
- * XCDs evenly loaded when the entries crowd into part of the grid. */
+/* Groups of kXcdGroup consecutive buckets go to one XCD, so that the runs of neighbouring buckets,
+ * which share cache lines of a row, meet in one L2; the groups themselves are dealt to the XCDs in
+ * turn, which keeps the XCDs evenly loaded when the entries crowd into part of the grid. */
 constexpr int kXcdGroup = 16;
-__device__ inline int xcd_bucket()
-{
-    const int x = (int)(blockIdx.x % kXcds), k = (int)(blockIdx.x / kXcds);
-    return ((k / kXcdGroup) * kXcds + x) * kXcdGroup + k % kXcdGroup;
-}
 static unsigned xcd_grid(int n_buckets)
 {
     const int per = kXcds * kXcdGroup;
@@ -1272,7 +1300,7 @@ __global__ __launch_bounds__(W * kWave) void k_place_sorted(
     float *__restrict__ t_values, Gate g)
 {
     if (gate_closed(g)) return;
-    const int b = xcd_bucket();
+    const int b = xcd_item<kXcdGroup>();
     if (b >= n_buckets) return;
     __shared__ uint32_t s_n[2][W][kBucketCols];   // entries per column of each wave's batch
     const int lane = lane_id(), wave = threadIdx.x >> 6;
@@ -1397,7 +1425,7 @@ __global__ __launch_bounds__(kWave) void k_place_any(
     int32_t *__restrict__ t_indices, float *__restrict__ t_values, Gate g)
 {
     if (gate_closed(g)) return;
-    const int b = xcd_bucket();
+    const int b = xcd_item<kXcdGroup>();
     if (b >= n_buckets) return;
     __shared__ uint32_t base[kBucketCols];
     __shared__ uint32_t cnt[kBucketCols];
