@@ -156,6 +156,14 @@ __global__ __launch_bounds__(kBlock) void k_zero_u32(uint32_t *__restrict__ x, i
  * not hold, and 64-entry sets whose columns do not ascend strictly (plain adds
  * need them distinct), go to memory one by one, and so does what is left of a
  * share whose rows lie too far apart for windows to pay.
+ *
+ * A group whose shares would have fewer than kDoseShare entries, or one of whose
+ * rows does not ascend from its first entry to its middle one and its last, takes no
+ * shares: its waves take whole rows, or pieces of rows, and send every entry to
+ * memory.  The searches of a window cost about what a thousand atomics do (2000 rows
+ * of 1000 entries: 13.6 us, 29.8 in shares of 500; 9000 shuffled rows of 300: 48 and
+ * 98; 64^3 and 8100 beamlets with a 1 cm cutoff, shares of 2245: 74 in windows, 143
+ * straight to memory).
  */
 constexpr int kDoseRows = 32;
 constexpr int kDoseWindow = 2048;              // 8 KB of LDS per wave: sixteen waves per CU
@@ -163,7 +171,8 @@ constexpr int kDoseSets = 4;                   // 64-entry sets whose loads are 
 constexpr int kDoseMinEntries = 64;            // windows pay with more entries than this each and at
 constexpr int kDoseSlack = 1024;               // least 4/3 per touched voxel, give or take a share's
                                                // ragged ends
-constexpr int kDoseShare = 128;                // fewest entries of a share
+constexpr int kDoseShare = 2048;               // fewest entries of a share
+constexpr int kDosePiece = 128;                // fewest entries of a piece of a row, on average
 constexpr int kDoseSpread = 8;                 // most columns per entry over which a share's rows lie
 constexpr int kDoseGuess = 24;                 // width of the first guess at a row's part of a window
 
@@ -211,18 +220,29 @@ __global__ __launch_bounds__(kBlock) void k_fluence_dose(const int64_t *__restri
     const int j = blockIdx.x * group + lane;
     const float wj = lane < group && j < n_rows ? w[j] : 0.0f;
     const int64_t e0 = wj != 0.0f ? indptr[j] : 0, e1 = wj != 0.0f ? indptr[j + 1] : 0;
-    const int64_t len = e1 - e0, all = wave_sum(len), waves = (int64_t)gridDim.y * kWavesPerBlock;
-    const int64_t me = (int64_t)blockIdx.y * kWavesPerBlock + wave;
-    int64_t p = e0, end = e1;
-    bool windowed = false;
-    if (all < kDoseShare * group) {   // short rows: whole ones
-        if (lane % waves != me) end = p;
-    } else {
-        const int64_t parts = min(waves, all / kDoseShare);
-        if (me >= parts) return;
-        p += len / parts * me + len % parts * me / parts;
-        end = e0 + len / parts * (me + 1) + len % parts * (me + 1) / parts;
+    const int64_t len = max(e1 - e0, (int64_t)0), all = wave_sum(len);
+    const int waves = (int)gridDim.y * kWavesPerBlock, me = (int)blockIdx.y * kWavesPerBlock + wave;
+    // where the k-th of n equal parts of the lane's row begins
+    auto cut = [&](int k, int n) { return e0 + len / n * k + len % n * k / n; };
+    int64_t p = e0, end = e0;
+    bool windowed = false, shares = all >= (int64_t)kDoseShare * waves;
+    if (shares) {
+        // the same rows and entries for every wave of the group: it takes shares, or it does not
+        const uint32_t a = len ? (uint32_t)indices[e0] : 0u, m = len ? (uint32_t)indices[e0 + (len >> 1)] : 0u;
+        const uint32_t b = len ? (uint32_t)indices[e1 - 1] : 0u;
+        p = cut(me, waves);
+        end = cut(me + 1, waves);
         windowed = dose_span(indices, p, end) <= kDoseSpread * wave_sum(end - p);
+        shares = __ballot(a > m || m > b) == 0;
+    }
+    if (!shares) {   // rows, or pieces of rows where there are more waves than rows
+        const int rows = min(group, n_rows - (int)blockIdx.x * group);
+        const int pieces = (int)max((int64_t)1, min((int64_t)(waves / rows), all / rows / kDosePiece));
+        const int step = pieces > 1 ? rows : min(waves, rows), r = me / pieces, k = me - r * pieces;
+        const bool mine = r < step && lane % step == r;
+        p = mine ? cut(k, pieces) : e0;
+        end = mine ? cut(k + 1, pieces) : e0;
+        windowed = false;
     }
     if (windowed) {
         for (int i = lane; i < kDoseWindow; i += kWave) acc[i] = 0.0f;
@@ -334,18 +354,24 @@ __global__ __launch_bounds__(kBlock) void k_fluence_dose(const int64_t *__restri
         out += wave_sum(touched);
         if (4 * out > 3 * seen + kDoseSlack || seen + kDoseSlack < windows * kDoseMinEntries) break;
     }
-    // what is left where windows do not pay, four rows at a time
-    for (uint64_t rows = __ballot(p < end); rows;) {
+    // what is left, straight to memory: four rows at a time, or two or four parts of a row
+    uint64_t rows = __ballot(p < end);
+    const int many = __popcll(rows), q = many >= 4 ? 1 : many >= 2 ? 2 : 4;
+    while (rows) {
         int64_t a[4], b[4];
         float wr[4];
-        bool more = false;
+        bool more = false, row = false;
+        int r = 0;
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            const int r = rows ? (int)__builtin_ctzll(rows) : 0;
-            a[k] = rows ? readlane64(p, r) : 0;
-            b[k] = rows ? readlane64(end, r) : 0;
+            if ((k & (q - 1)) == 0) {
+                row = rows != 0;
+                r = row ? (int)__builtin_ctzll(rows) : 0;
+                rows &= rows - 1;
+            }
+            a[k] = row ? readlane64(p, r) + kWave * (k & (q - 1)) : 0;
+            b[k] = row ? readlane64(end, r) : 0;
             wr[k] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(wj), r));
-            rows &= rows - 1;
             more = more || a[k] < b[k];
         }
         while (more) {
@@ -357,7 +383,7 @@ __global__ __launch_bounds__(kBlock) void k_fluence_dose(const int64_t *__restri
                 const bool in = a[k] + lane < b[k];
                 i[k] = in ? (uint32_t)indices[a[k] + lane] : 0xffffffffu;
                 v[k] = in ? values[a[k] + lane] : 0.0f;
-                a[k] += kWave;
+                a[k] += q * kWave;
                 more = more || a[k] < b[k];
             }
 #pragma unroll

@@ -38,3 +38,12 @@ def test_gradient_of_many_short_rows():
     many, few = _rows(9000, 50, n), _rows(2000, 225, n)
     r = torch.rand(n, device="cuda")
     assert _us(lambda: many.gradient(r)) < 1.8 * _us(lambda: few.gradient(r))
+
+
+def test_dose_of_rows_of_a_thousand_entries():
+    """2000 rows of 1000 entries: 13.6 us, where 2000 rows of 100 take 10 (29.8 in shares too short for windows)."""
+    import torch
+    n = 100000
+    rows, short = _rows(2000, 1000, n), _rows(2000, 100, n)
+    w = torch.rand(2000, device="cuda")
+    assert _us(lambda: rows.dose(w)) < 2.0 * _us(lambda: short.dose(w))
