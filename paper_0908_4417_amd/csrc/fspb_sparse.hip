@@ -554,8 +554,10 @@ __global__ __launch_bounds__(BLOCK) void k_fluence_gradient(const int64_t *__res
  * because many rows are shorter than a step of 16 or 32 (64x64x64, one beam of
  * 100: 8 us, 13 with 16 lanes, 25 with 32).  w comes from LDS where a CU can hold
  * four copies and so all its waves (128^3, 9 beams of 900: 1020 us, gathered
- * through the cache 1202; 12500 beamlets 117 and 102), and workgroups stay for
- * many rows: 8191 of them (the slab with 4095: 1082 us, 8191: 1028, 12287: 1016; a
+ * through the cache 1202; 12500 beamlets 117 and 102) and the matrix has a third of an entry for
+ * each word copied (64^3, 8100 beamlets: with 2.5 entries per word 144 and 184, with 0.27 23.3 and
+ * 18.9, with 0.02 13.5 and 7.6; 9000 on 2e6 voxels, 0.49: 102 and 87 where neighbouring voxels
+ * meet the same beamlets, 105 and 158 where any), and workgroups stay for many rows: 8191 of them (the slab with 4095: 1082 us, 8191: 1028, 12287: 1016; a
  * pelvis 910, 896, 1016), an odd number, so that no workgroup's rows keep the same
  * place in the grid's lines (a pelvis with 8192: 1231).
  * 128^3, 9 beams of 900, 6.5e8 entries: 1028 us (5.1 TB/s), 1469 with 16 lanes per
@@ -568,17 +570,15 @@ constexpr int kVoxelRows = kVoxelBlock / kVoxelLanes;
 constexpr int kVoxelStep = 4 * kVoxelLanes;
 constexpr int kVoxelLdsWords = 10240;              // 40 KB: four workgroups, 32 waves per CU
 constexpr int kVoxelGroups = 8191;
+constexpr int kVoxelReuse = 3;                     // words of w copied to LDS per entry, at most
+constexpr int kVoxelFewWords = 1024;               // copied in any case: the entries' number is one load later
 template <bool LDS>
-__global__ __launch_bounds__(kVoxelBlock) void k_voxel_dose(const int64_t *__restrict__ t_indptr,
-                                                            const int32_t *__restrict__ t_indices,
-                                                            const float *__restrict__ t_values, int n_voxels, int n_w,
-                                                            const float *__restrict__ w, float *__restrict__ dose)
+__device__ __attribute__((always_inline)) inline void voxel_rows(const int64_t *__restrict__ t_indptr,
+                                                                 const int32_t *__restrict__ t_indices,
+                                                                 const float *__restrict__ t_values, int n_voxels,
+                                                                 int n_w, const float *w, float *__restrict__ dose)
 {
     extern __shared__ float s_w[];
-    if (LDS) {
-        for (int j = threadIdx.x; j < n_w; j += kVoxelBlock) s_w[j] = w[j];
-        __syncthreads();
-    }
     const float *wt = LDS ? s_w : w;
     const int l = threadIdx.x & (kVoxelLanes - 1);
     const uint32_t n = (uint32_t)n_w;
@@ -649,6 +649,28 @@ __global__ __launch_bounds__(kVoxelBlock) void k_voxel_dose(const int64_t *__res
         i = in;
         e0 = n0;
         e1 = n1;
+    }
+}
+
+/* Where w is read: through the cache, from LDS, or by the number of entries (kVoxelReuse).  Eight waves
+ * per SIMD: with 66 registers instead of 64 there were seven (240 rows of 8e4 entries on 128^3: 60 us
+ * instead of 49). */
+enum class WHome { kCache, kLds, kEither };
+template <WHome HOME>
+__global__ __launch_bounds__(kVoxelBlock, 8) void k_voxel_dose(const int64_t *__restrict__ t_indptr,
+                                                               const int32_t *__restrict__ t_indices,
+                                                               const float *__restrict__ t_values, int n_voxels,
+                                                               int n_w, const float *__restrict__ w,
+                                                               float *__restrict__ dose)
+{
+    extern __shared__ float s_w[];
+    if (HOME == WHome::kLds || (HOME == WHome::kEither && (int64_t)n_w * gridDim.x <=
+                                                              kVoxelReuse * (t_indptr[n_voxels] - t_indptr[0]))) {
+        for (int j = threadIdx.x; j < n_w; j += kVoxelBlock) s_w[j] = w[j];
+        __syncthreads();
+        voxel_rows<true>(t_indptr, t_indices, t_values, n_voxels, n_w, w, dose);
+    } else {
+        voxel_rows<false>(t_indptr, t_indices, t_values, n_voxels, n_w, w, dose);
     }
 }
 
@@ -1024,12 +1046,16 @@ hipError_t launch_voxel_dose(const int64_t *t_indptr, const int32_t *t_indices, 
                              int n_w, const float *w, float *dose, hipStream_t s)
 {
     const unsigned blocks = std::min(blocks_of((int64_t)n_voxels, kVoxelRows), (unsigned)kVoxelGroups);
-    if (n_w <= kVoxelLdsWords)
-        hipLaunchKernelGGL(k_voxel_dose<true>, dim3(blocks), dim3(kVoxelBlock), sizeof(float) * (size_t)n_w, s,
-                           t_indptr, t_indices, t_values, n_voxels, n_w, w, dose);
+    const size_t copy = sizeof(float) * (size_t)n_w;
+    if (n_w <= kVoxelFewWords)
+        hipLaunchKernelGGL(k_voxel_dose<WHome::kLds>, dim3(blocks), dim3(kVoxelBlock), copy, s, t_indptr, t_indices,
+                           t_values, n_voxels, n_w, w, dose);
+    else if (n_w <= kVoxelLdsWords)
+        hipLaunchKernelGGL(k_voxel_dose<WHome::kEither>, dim3(blocks), dim3(kVoxelBlock), copy, s, t_indptr, t_indices,
+                           t_values, n_voxels, n_w, w, dose);
     else
-        hipLaunchKernelGGL(k_voxel_dose<false>, dim3(blocks), dim3(kVoxelBlock), 0, s, t_indptr, t_indices, t_values,
-                           n_voxels, n_w, w, dose);
+        hipLaunchKernelGGL(k_voxel_dose<WHome::kCache>, dim3(blocks), dim3(kVoxelBlock), 0, s, t_indptr, t_indices,
+                           t_values, n_voxels, n_w, w, dose);
     return hipGetLastError();
 }
 
