@@ -1100,7 +1100,8 @@ struct Flags {
     int32_t need_counts;   // entries per column counted by atomics (entry path, unsorted rows)
     int32_t sorted;        // run path with masks (rows ascending)
     int32_t any;           // run path for rows in any column order
-    int32_t pad[9];
+    int32_t few_runs;      // too few runs to a bucket for four waves
+    int32_t pad[8];
 };
 static_assert(sizeof(Flags) == 64, "one slot");
 
@@ -1186,8 +1187,9 @@ __global__ __launch_bounds__(kBlock) void k_run_count(const int64_t *__restrict_
 static_assert(kRunBlock % (kRowChunks * kWave) == 0, "blocks end with a group of chunks");
 
 /* The path flags (one thread): a run path when the runs are at most half the
- * entries, with masks when the rows ascend; else the radix sort of the entries. */
-__global__ void k_run_sizes(const int64_t *__restrict__ n_runs, int64_t nnz, Flags *__restrict__ fl)
+ * entries, with masks when the rows ascend; else the radix sort of the entries.
+ * many_runs: fewer are few for the placement. */
+__global__ void k_run_sizes(const int64_t *__restrict__ n_runs, int64_t nnz, int64_t many_runs, Flags *__restrict__ fl)
 {
     const int64_t R = *n_runs;
     const int32_t use = 2 * R <= nnz ? 1 : 0, uns = fl->unsorted ? 1 : 0;
@@ -1196,6 +1198,7 @@ __global__ void k_run_sizes(const int64_t *__restrict__ n_runs, int64_t nnz, Fla
     fl->need_counts = (!use || uns) ? 1 : 0;
     fl->sorted = (use && !uns) ? 1 : 0;
     fl->any = (use && uns) ? 1 : 0;
+    fl->few_runs = R < many_runs ? 1 : 0;
 }
 
 /*
@@ -1346,23 +1349,19 @@ typedef float vf4u __attribute__((ext_vector_type(4), aligned(4)));
  * against 3.97 with each batch's entries reordered in LDS.
  */
 template <int W>
-__global__ __launch_bounds__(W * kWave) void k_place_sorted(
-    const float *__restrict__ values, int n_voxels, int n_buckets, const int64_t *__restrict__ b_ptr,
-    const Run *__restrict__ runs, const int64_t *__restrict__ t_indptr, uint32_t nnz, int32_t *__restrict__ t_indices,
-    float *__restrict__ t_values, Gate g)
+__device__ __attribute__((always_inline)) inline void place_bucket(
+    int b, int wave, uint32_t (*s_n)[W][kBucketCols], const float *__restrict__ values, int n_voxels,
+    const int64_t *__restrict__ b_ptr, const Run *__restrict__ runs, const int64_t *__restrict__ t_indptr, uint32_t nnz,
+    int32_t *__restrict__ t_indices, float *__restrict__ t_values)
 {
-    if (gate_closed(g)) return;
-    const int b = xcd_item<kXcdGroup>();
-    if (b >= n_buckets) return;
-    __shared__ uint32_t s_n[2][W][kBucketCols];   // entries per column of each wave's batch
-    const int lane = lane_id(), wave = threadIdx.x >> 6;
+    const int lane = lane_id();
     const int64_t q0 = b_ptr[b], q1 = b_ptr[b + 1];
     // lane c: next output position of column c
     const int mine = (b << kBucketShift) + lane;
     uint32_t pos = lane < kBucketCols && mine < n_voxels ? (uint32_t)t_indptr[mine] : 0u;
 
     constexpr int kBatch = W * kWave;
-    int64_t q = q0 + threadIdx.x;
+    int64_t q = q0 + wave * kWave + lane;
     Run next = q < q1 ? runs[q] : make_uint4(0u, 0u, 0u, 0u);
     int turn = 0;
     for (int64_t qb = q0; qb < q1; qb += kBatch, turn ^= 1) {
@@ -1402,7 +1401,8 @@ __global__ __launch_bounds__(W * kWave) void k_place_sorted(
             n = lane == c ? k : n;
         }
         if (lane < kBucketCols) s_n[turn][wave][lane] = n;
-        __syncthreads();   // the buffers alternate: one barrier a batch
+        if (W > 1) __syncthreads();   // the buffers alternate: one barrier a batch
+        else wave_lds_fence();
         uint32_t at = pos;
 #pragma unroll
         for (int w = 0; w < W; ++w) {
@@ -1422,6 +1422,27 @@ __global__ __launch_bounds__(W * kWave) void k_place_sorted(
                 (t_values + p)[rank] = v[c];
             }
         }
+    }
+}
+
+/* One bucket per workgroup, or (few: where the flag says so) per wave. */
+template <int W>
+__global__ __launch_bounds__(W * kWave) void k_place_sorted(
+    const float *__restrict__ values, int n_voxels, int n_buckets, const int64_t *__restrict__ b_ptr,
+    const Run *__restrict__ runs, const int64_t *__restrict__ t_indptr, uint32_t nnz, int32_t *__restrict__ t_indices,
+    float *__restrict__ t_values, const int32_t *__restrict__ few, Gate g)
+{
+    if (gate_closed(g)) return;
+    __shared__ uint32_t s_n[2 * W * kBucketCols];   // entries per column of each wave's batch
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), b = xcd_item<kXcdGroup>();
+    if (W > 1 && *few) {
+        const int bw = b * W + wave;   // a barrier is not met: each wave goes through its own bucket
+        if (bw < n_buckets)
+            place_bucket<1>(bw, 0, reinterpret_cast<uint32_t(*)[1][kBucketCols]>(s_n + 2 * kBucketCols * wave), values,
+                            n_voxels, b_ptr, runs, t_indptr, nnz, t_indices, t_values);
+    } else if (b < n_buckets) {
+        place_bucket<W>(b, wave, reinterpret_cast<uint32_t(*)[W][kBucketCols]>(s_n), values, n_voxels, b_ptr, runs,
+                        t_indptr, nnz, t_indices, t_values);
     }
 }
 
@@ -1666,8 +1687,12 @@ static hipError_t sort_runs(Run *a, Run *b, Count n, int64_t n_max, int passes, 
 // three, so that the open cache lines stay in L2 (1e4 entries per bucket: placement 3.03 ms against
 // 3.39 with as many as fit and 3.83 with one wave each; whole transposes of 715 per bucket 0.64 ms
 // against 0.68 with one wave); small ones, whose latency counts, by one wave and as many as fit
-// (290 per bucket 0.33 against 0.38, 160 per bucket 0.23 against 0.34).
+// (290 per bucket 0.33 against 0.38, 160 per bucket 0.23 against 0.34).  Four waves take 256 runs at
+// a time, so a bucket must also have runs for them, which only the device knows: rows of consecutive
+// columns have one to a row (9000 rows of 4000 over 2e6 columns, 18 runs to a bucket of 576 entries:
+// 0.4 ms with a wave to each bucket, 0.57 with four; 38 runs and 683 entries 0.56 with four, 0.58).
 constexpr int64_t kPlaceMany = 512;              // entries per bucket
+constexpr int64_t kPlaceRuns = 32;               // runs per bucket
 constexpr unsigned kPlaceReserve = 45 * 1024;
 
 hipError_t launch_transpose(const int64_t *indptr, const int32_t *indices, const float *values, int n_rows,
@@ -1705,12 +1730,12 @@ hipError_t launch_transpose(const int64_t *indptr, const int32_t *indices, const
                                 s)) != hipSuccess)
         return e;
     const Count n_runs{0, run_ptr + pieces};
-    hipLaunchKernelGGL(k_run_sizes, dim3(1), dim3(1), 0, s, n_runs.dev, nnz, fl);
+    const int nb = (n_voxels + kBucketCols - 1) >> kBucketShift;
+    hipLaunchKernelGGL(k_run_sizes, dim3(1), dim3(1), 0, s, n_runs.dev, nnz, kPlaceRuns * nb, fl);
     const Gate runs{&fl->use_runs, 1}, entries{&fl->use_runs, 0}, counted{&fl->need_counts, 1},
         masked{&fl->sorted, 1}, any{&fl->any, 1};
 
     // run paths: at most nnz / 2 records of 16 bytes, in the space of key, row and val of each side
-    const int nb = (n_voxels + kBucketCols - 1) >> kBucketShift;
     const int64_t half = (nnz + 1) / 2;
     Run *ra = reinterpret_cast<Run *>(key[0]), *rb = reinterpret_cast<Run *>(key[1]), *sorted = nullptr;
     int64_t *bptr = reinterpret_cast<int64_t *>(ws + L.bptr);
@@ -1734,10 +1759,10 @@ hipError_t launch_transpose(const int64_t *indptr, const int32_t *indices, const
 
     if (nnz >= kPlaceMany * nb)
         hipLaunchKernelGGL(k_place_sorted<4>, dim3(xcd_grid(nb)), dim3(4 * kWave), kPlaceReserve, s, values, n_voxels,
-                           nb, bptr, sorted, t_indptr, (uint32_t)nnz, t_indices, t_values, masked);
+                           nb, bptr, sorted, t_indptr, (uint32_t)nnz, t_indices, t_values, &fl->few_runs, masked);
     else
         hipLaunchKernelGGL(k_place_sorted<1>, dim3(xcd_grid(nb)), dim3(kWave), 0, s, values, n_voxels, nb, bptr,
-                           sorted, t_indptr, (uint32_t)nnz, t_indices, t_values, masked);
+                           sorted, t_indptr, (uint32_t)nnz, t_indices, t_values, nullptr, masked);
     hipLaunchKernelGGL(k_place_any, dim3(xcd_grid(nb)), dim3(kWave), 0, s, indices, values, n_voxels, nb, bptr, sorted,
                        t_indptr, (uint32_t)nnz, t_indices, t_values, any);
     if ((e = hipGetLastError()) != hipSuccess) return e;

@@ -64,3 +64,10 @@ def test_voxel_dose_of_short_rows():
         T, w = VoxelCSR(ip, idx, val, beamlets), torch.rand(beamlets, device="cuda")
         t[beamlets] = _us(lambda: T.dose(w))
     assert t[8100] < 1.35 * t[100]
+
+
+def test_transpose_of_rows_without_gaps():
+    """18 runs to a bucket of 576 entries (0.39 ms) take less than twice their half (0.26 ms; 0.57 with four waves a bucket)."""
+    n = 2000000
+    D, half = _rows(9000, 4000, n), _rows(4500, 4000, n)
+    assert _us(D.transpose, 10) < 1.8 * _us(half.transpose, 10)
