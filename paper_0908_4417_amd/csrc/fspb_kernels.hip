@@ -1511,9 +1511,11 @@ hipError_t launch_prep(const PlanDev *dplan, const PlanDev &h, hipStream_t s)
     return hipGetLastError();
 }
 
-// A workgroup per beamlet where one wave per beamlet leaves wave slots of the 1024 SIMDs empty
-// (715 beamlets: plan 191 us, one wave each 215; 12500: 398 and 381), within 32 KB of tile sums.
-constexpr int kCountWide = 8192;
+// A workgroup per beamlet where one wave per beamlet leaves most wave slots of the 1024 SIMDs empty,
+// within 32 KB of tile sums.  Mask, counts and tables of a 128^3 plan of 1080 beamlets: 33 us, one wave
+// each 50; of 2520: 60 and 57; 5940: 116 and 95; 8100: 156 and 125; on 256x256x100 1080: 55 and 84,
+// 2520: 98 and 95, 5184: 163 and 140.
+constexpr int kCountWide = 2048;
 constexpr int kCountTiles = 8192;
 
 hipError_t launch_trace(const PlanDev *dplan, const PlanDev &h, bool count, bool depth, hipStream_t s)

@@ -71,3 +71,19 @@ def test_transpose_of_rows_without_gaps():
     n = 2000000
     D, half = _rows(9000, 4000, n), _rows(4500, 4000, n)
     assert _us(D.transpose, 10) < 1.8 * _us(half.transpose, 10)
+
+
+def test_counts_of_many_beamlets():
+    """Mask, counts and tables: 8100 beamlets take less than 8370 (125 and 129 us; 156 with a workgroup a beamlet)."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import fspb_inputs as fi
+    from paper_0908_4417_amd import Plan
+    g = fi.slab_phantom(3, n=(128, 128, 128), spacing=(0.25, 0.25, 0.25))
+    t = {}
+    for nv in (30, 31):
+        beams = fi.coplanar_beams(9, (0.13, -0.07, 0.05), 100.0, 0.5, 0.5, 30, nv)
+        plan = Plan(fi.Problem("counts", g, beams, fi.default_kernel(3)), "cuda:0")
+        t[nv] = _us(plan.raytrace, 30)
+    assert t[30] < 1.08 * t[31]
