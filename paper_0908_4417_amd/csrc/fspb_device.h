@@ -178,9 +178,16 @@ hipError_t launch_batch_wave(int stage, const PlanDev *const *plans, const int64
                              int grid, hipStream_t s);   // stage 0 prep, 1 raytrace, 2 count
 hipError_t launch_batch_scan(const PlanDev *const *plans, const OutDev *outs, int n_plans, hipStream_t s);
 hipError_t launch_batch_reset(int *counters, int n, hipStream_t s);
+/* What the plans of a batch need of a fill workgroup's LDS, at most. */
+struct BatchLds {
+    size_t whole = 0;        // fill_shared_bytes
+    size_t rest = 0;         // fill_dynamic_bytes
+    bool compact = false;    // some plan has the compact erf table
+    bool mirrored = false;   // some plan has the mirrored one
+};
 /* per_item work items per queue fetch; tile_group consecutive tiles per wave step. */
 hipError_t launch_batch_fill(int K, int W, const PlanDev *const *plans, const OutDev *outs, const int2 *items,
-                             int n_items, int *counter, int per_item, int tile_group, int grid, size_t lds,
+                             int n_items, int *counter, int per_item, int tile_group, int grid, const BatchLds &lds,
                              hipStream_t s);
 
 }  // namespace fspb

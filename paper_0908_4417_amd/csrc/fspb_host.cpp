@@ -1138,7 +1138,7 @@ struct fspb_batch {
     std::vector<OutDev> outs;
     std::vector<bool> bound;
     int32_t max_terms = 1;
-    size_t lds = 0;
+    fspb::BatchLds lds;
     int cus = 256;
     fspb_batch_config cfg{4, 4, 0, 0, 0.0f, fspb::kRowsPerTile, 1, 0};
     hipStream_t cap_stream = nullptr;
@@ -1292,7 +1292,9 @@ fspb_status fspb_batch_create(fspb_plan *const *plans, int32_t n_plans, void *wo
         start[1][i + 1] = start[1][i] + h.n_beamlets;
         start[2][i + 1] = start[2][i] + h.n_beamlets;
         b->max_terms = std::max(b->max_terms, h.n_terms);
-        b->lds = std::max(b->lds, fspb::fill_dynamic_bytes(h));   // beside an erf table of either form
+        b->lds.whole = std::max(b->lds.whole, fspb::fill_shared_bytes(h));
+        b->lds.rest = std::max(b->lds.rest, fspb::fill_dynamic_bytes(h));
+        (fspb::fill_mirrored_erf(h) ? b->lds.mirrored : b->lds.compact) = true;
         b->outs[i].overflow = plans[i]->d_overflow;
     }
     for (int st = 0; st < kWaveStages; ++st) b->total[st] = start[st][n_plans];

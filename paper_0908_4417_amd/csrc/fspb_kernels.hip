@@ -965,10 +965,18 @@ __device__ inline int readlane(int v, int lane) { return __builtin_amdgcn_readla
  * K = unrolled term count; GUARD: stop at P.n_terms (plans of mixed K);
  * EM: how erf is read (erf_mirrored_mode).
  */
+/* The fill's LDS beside its tables: one copy for all modes of a kernel. */
+template <int W>
+struct FillShared {
+    RowGeom geom;   // the beamlet's
+    int wsum[W];
+};
+
 /* tile_group: consecutive 64-row tiles a wave takes per step (the batched fill's tuned shape);
  * part, parts: this workgroup's share of the beamlet, the part-th W of every parts W steps. */
 template <int K, int W, bool GUARD, bool SURR, bool GEN = false, int EM = 0>
-__device__ __attribute__((always_inline)) inline void fill_beamlet(const PlanDev &P, const OutDev &O, int j, float2 *s_erf, unsigned char *smem,
+__device__ __attribute__((always_inline)) inline void fill_beamlet(const PlanDev &P, const OutDev &O, int j, FillShared<W> &fs,
+                                                             float2 *s_erf, unsigned char *smem,
                                                              int tile_group = 1, int part = 0, int parts = 1)
 {
     const BeamletRec &R = P.rec[j];
@@ -1031,9 +1039,9 @@ __device__ __attribute__((always_inline)) inline void fill_beamlet(const PlanDev
     float2 *s_tab = reinterpret_cast<float2 *>(smem);
     float2 *s_pdd = s_tab + P.max_table;
     int *s_tpre = reinterpret_cast<int *>(s_pdd + n_pdd);
-    __shared__ int wsum[W];
+    int *wsum = fs.wsum;
     // the beamlet's VOI row coefficients, read by every tile (LDS keeps them out of registers)
-    __shared__ RowGeom s_geom;
+    RowGeom &s_geom = fs.geom;
     const int c1_pos = __builtin_amdgcn_readfirstlane(R.c1_pos), c1_neg = __builtin_amdgcn_readfirstlane(R.c1_neg);
     // surrogate: its parameters after the tile prefix, the beamlet's width term in the first bias,
     // and W2 fragments in registers
@@ -1407,9 +1415,10 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(SURR ? 2
 {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ __align__(16) float2 s_erf[erf_pairs(EM)];   // at a fixed address: see erf_diff
+    __shared__ FillShared<kWavesPerBlock> fs;
     // launched before the host has read the plan's total: write nothing if it does not fit
     if (out.check_nnz && *plans[0].nnz > out.capacity) return;
-    fill_beamlet<K, kWavesPerBlock, false, SURR, GEN, EM>(plans[0], out, out.row0 + (int)blockIdx.x, s_erf, smem, 1,
+    fill_beamlet<K, kWavesPerBlock, false, SURR, GEN, EM>(plans[0], out, out.row0 + (int)blockIdx.x, fs, s_erf, smem, 1,
                                                          (int)blockIdx.y, (int)gridDim.y);
 }
 
@@ -1454,19 +1463,31 @@ __global__ __launch_bounds__(kScanBlock) void kp_scan(const PlanDev *const *__re
     scan_plan(*plans[blockIdx.x], outs[blockIdx.x].indptr);
 }
 
+// where a batch's fill keeps the erf table: the compact or the mirrored one at a fixed address, or the
+// plan's own form in the dynamic part
+enum class BatchErf { kCompact, kMirrored, kPlan };
+
 // amdgpu_waves_per_eu(4): a register budget that leaves room for at least four waves per SIMD
 // (it is a lower bound on occupancy, not a cap)
 // Work items (plan, beamlet) come from a queue, per_item consecutive ones per fetch; a wave
 // takes tile_group consecutive tiles of a beamlet per step.
-template <int K, int W>
+// HOME: where the erf table lies (choose_batch_erf).
+template <int K, int W, BatchErf HOME>
 __global__ __launch_bounds__(W * kWave) __attribute__((amdgpu_waves_per_eu(4))) void kp_fill(const PlanDev *const *__restrict__ plans,
                                                      const OutDev *__restrict__ outs,
                                                      const int2 *__restrict__ items, int n_items,
                                                      int *__restrict__ counter, int per_item, int tile_group)
 {
     extern __shared__ __align__(16) unsigned char smem[];
-    __shared__ __align__(16) float2 s_erf[erf_pairs(4)];
+    __shared__ FillShared<W> fs;
     __shared__ int s_item;
+    float2 *s_erf;
+    if constexpr (HOME == BatchErf::kPlan) {
+        s_erf = reinterpret_cast<float2 *>(smem);
+    } else {
+        __shared__ __align__(16) float2 s_fixed[erf_pairs(HOME == BatchErf::kMirrored ? 4 : 0)];
+        s_erf = s_fixed;
+    }
     for (;;) {
         if (threadIdx.x == 0) s_item = atomicAdd(counter, 1);
         __syncthreads();
@@ -1477,13 +1498,16 @@ __global__ __launch_bounds__(W * kWave) __attribute__((amdgpu_waves_per_eu(4))) 
         for (int w = w0; w < w1; ++w) {
             const int2 it = items[w];
             const PlanDev &P = *plans[it.x];
-            // each plan in the erf table form of its own fill (identical results to it)
-            switch (P.erf_mode) {
-            case 4: fill_beamlet<K, W, true, false, false, 4>(P, outs[it.x], it.y, s_erf, smem, tile_group); break;
-            case 3: fill_beamlet<K, W, true, false, false, 3>(P, outs[it.x], it.y, s_erf, smem, tile_group); break;
-            case 2: fill_beamlet<K, W, true, false, false, 2>(P, outs[it.x], it.y, s_erf, smem, tile_group); break;
-            case 1: fill_beamlet<K, W, true, false, false, 1>(P, outs[it.x], it.y, s_erf, smem, tile_group); break;
-            default: fill_beamlet<K, W, true, false, false, 0>(P, outs[it.x], it.y, s_erf, smem, tile_group); break;
+            // each plan in the erf mode of its own fill (identical results to it)
+            const int em = HOME == BatchErf::kCompact ? 0 : P.erf_mode;
+            unsigned char *rest = smem;
+            if (HOME == BatchErf::kPlan) rest += sizeof(float2) * (em ? erf_pairs(1) : erf_pairs(0));
+            switch (em) {
+            case 4: fill_beamlet<K, W, true, false, false, 4>(P, outs[it.x], it.y, fs, s_erf, rest, tile_group); break;
+            case 3: fill_beamlet<K, W, true, false, false, 3>(P, outs[it.x], it.y, fs, s_erf, rest, tile_group); break;
+            case 2: fill_beamlet<K, W, true, false, false, 2>(P, outs[it.x], it.y, fs, s_erf, rest, tile_group); break;
+            case 1: fill_beamlet<K, W, true, false, false, 1>(P, outs[it.x], it.y, fs, s_erf, rest, tile_group); break;
+            default: fill_beamlet<K, W, true, false, false, 0>(P, outs[it.x], it.y, fs, s_erf, rest, tile_group); break;
             }
             __syncthreads();
         }
@@ -1657,39 +1681,78 @@ hipError_t launch_batch_reset(int *counters, int n, hipStream_t s)
     return hipGetLastError();
 }
 
-template <int K>
-static hipError_t launch_kp_fill_k(int W, const PlanDev *const *plans, const OutDev *outs, const int2 *items,
-                                   int n_items, int *counter, int per_item, int tile_group, int grid, size_t lds,
-                                   hipStream_t s)
+template <int K, int W>
+static const void *batch_kernel_ptr_kw(BatchErf home)
 {
-    const dim3 g(grid);
-    switch (W) {
-    case 2:
-        hipLaunchKernelGGL((kp_fill<K, 2>), g, dim3(2 * kWave), lds, s, plans, outs, items, n_items, counter, per_item,
-                           tile_group);
-        break;
-    case 8:
-        hipLaunchKernelGGL((kp_fill<K, 8>), g, dim3(8 * kWave), lds, s, plans, outs, items, n_items, counter, per_item,
-                           tile_group);
-        break;
-    default:
-        hipLaunchKernelGGL((kp_fill<K, 4>), g, dim3(4 * kWave), lds, s, plans, outs, items, n_items, counter, per_item,
-                           tile_group);
-        break;
+    switch (home) {
+    case BatchErf::kCompact: return (const void *)kp_fill<K, W, BatchErf::kCompact>;
+    case BatchErf::kPlan: return (const void *)kp_fill<K, W, BatchErf::kPlan>;
+    default: return (const void *)kp_fill<K, W, BatchErf::kMirrored>;
     }
-    return hipGetLastError();
+}
+
+template <int K>
+static const void *batch_kernel_ptr_k(int W, BatchErf home)
+{
+    switch (W) {
+    case 2: return batch_kernel_ptr_kw<K, 2>(home);
+    case 8: return batch_kernel_ptr_kw<K, 8>(home);
+    default: return batch_kernel_ptr_kw<K, 4>(home);
+    }
+}
+
+static const void *batch_kernel_ptr(int K, int W, BatchErf home)
+{
+    switch (K) {
+    case 1: return batch_kernel_ptr_k<1>(W, home);
+    case 2: return batch_kernel_ptr_k<2>(W, home);
+    case 3: return batch_kernel_ptr_k<3>(W, home);
+    default: return batch_kernel_ptr_k<4>(W, home);
+    }
+}
+
+/* Workgroups of a batch's fill per CU: the runtime's limit from registers and waves, and that of the
+ * LDS, which gfx950 hands out 1280 bytes at a time; 0 if a query fails. */
+static int batch_groups_per_cu(const void *f, int threads, size_t lds)
+{
+    int n = 0, dev = 0, lds_cu = 0;
+    hipFuncAttributes attr{};
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, f, threads, 0) != hipSuccess ||
+        hipFuncGetAttributes(&attr, f) != hipSuccess || hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&lds_cu, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor, dev) != hipSuccess) {
+        (void)hipGetLastError();
+        return 0;
+    }
+    return std::min(n, lds_cu / (int)((lds + attr.sharedSizeBytes + 1279) / 1280 * 1280));
+}
+
+/*
+ * Where a batch's fill keeps the erf table.  A batch of compact plans has room for the compact table
+ * only (eight plans 1.14 ms, 1.21 with room for the mirrored one).  One with mirrored plans has it at a
+ * fixed address, as the lookups want it (four plans of each form 1.16 ms, 1.17 in the dynamic part,
+ * where each lookup adds the table's address; six of 28 KB and six of 25 2.21 and 2.23): the room is
+ * that of the mirrored table also beside a compact plan's other tables, which are the larger ones.
+ * Where that costs workgroups per CU, each plan's own form lies in front of its tables instead (six
+ * plans of 34.8 KB and six of 24.8: 2.62 ms with three workgroups per CU, 2.26 with four; of 46.1 and
+ * 24.8: 3.60 with two, 2.70 with three).
+ */
+static BatchErf choose_batch_erf(int K, int W, const BatchLds &lds)
+{
+    if (!lds.mirrored) return BatchErf::kCompact;
+    if (!lds.compact) return BatchErf::kMirrored;
+    const int fixed = batch_groups_per_cu(batch_kernel_ptr(K, W, BatchErf::kMirrored), W * kWave, lds.rest);
+    const int own = batch_groups_per_cu(batch_kernel_ptr(K, W, BatchErf::kPlan), W * kWave, lds.whole);
+    return fixed > 0 && fixed >= own ? BatchErf::kMirrored : BatchErf::kPlan;
 }
 
 hipError_t launch_batch_fill(int K, int W, const PlanDev *const *plans, const OutDev *outs, const int2 *items,
-                             int n_items, int *counter, int per_item, int tile_group, int grid, size_t lds,
+                             int n_items, int *counter, int per_item, int tile_group, int grid, const BatchLds &lds,
                              hipStream_t s)
 {
-    switch (K) {
-    case 1: return launch_kp_fill_k<1>(W, plans, outs, items, n_items, counter, per_item, tile_group, grid, lds, s);
-    case 2: return launch_kp_fill_k<2>(W, plans, outs, items, n_items, counter, per_item, tile_group, grid, lds, s);
-    case 3: return launch_kp_fill_k<3>(W, plans, outs, items, n_items, counter, per_item, tile_group, grid, lds, s);
-    default: return launch_kp_fill_k<4>(W, plans, outs, items, n_items, counter, per_item, tile_group, grid, lds, s);
-    }
+    const BatchErf home = choose_batch_erf(K, W, lds);
+    void *args[] = {&plans, &outs, &items, &n_items, &counter, &per_item, &tile_group};
+    return hipLaunchKernel(batch_kernel_ptr(K, W, home), dim3(grid), dim3(W * kWave), args,
+                           home == BatchErf::kPlan ? lds.whole : lds.rest, s);
 }
 
 /*

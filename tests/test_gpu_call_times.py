@@ -87,3 +87,27 @@ def test_counts_of_many_beamlets():
         plan = Plan(fi.Problem("counts", g, beams, fi.default_kernel(3)), "cuda:0")
         t[nv] = _us(plan.raytrace, 30)
     assert t[30] < 1.08 * t[31]
+
+
+def test_batch_of_both_erf_forms():
+    """Six plans with the compact erf table and 46 KB of LDS beside six with the mirrored one and 25 take less than the two
+    batches apart (2.69 ms and 1.95 + 0.90): room for the mirrored table in both leaves two workgroups per CU instead of
+    three (3.57 ms)."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import fspb_inputs as fi
+    from paper_0908_4417_amd import Batch, Plan
+    thin = fi.water_phantom((96, 96, 100), (0.4, 0.4, 0.023))
+    body = fi.pelvis_phantom(3)
+    iso = (0.13, -0.07, 0.05)
+    plans = lambda form: [Plan(fi.Problem("thin", thin, fi.coplanar_beams(3, iso, 100.0, 0.5, 0.5, 8, 2, start_deg=5.0),
+                                          fi.default_kernel(k)), "cuda:0", erf_form=form) for k in range(6)]
+    other = lambda form: [Plan(fi.Problem("body", body, fi.coplanar_beams(2, iso, 100.0, 0.25, 0.25, 24, 24, start_deg=5.0),
+                                          fi.default_kernel(k)), "cuda:0", erf_form=form) for k in range(6)]
+    t = []
+    for ps in (plans("compact") + other("mirrored"), other("mirrored"), plans("compact")):
+        batch = Batch(ps)
+        batch.set_config(4, 4, 0)
+        t.append(_us(batch.run, 10))
+    assert t[0] < 1.1 * (t[1] + t[2])
