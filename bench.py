@@ -16,7 +16,9 @@ second of wall clock over the K timed steps (whole-job throughput) and
 `ms_per_step` = wall clock per plan in that loop.  `ms_per_step_one_stream`
 is the same loop on one stream (one plan at a time), and
 `device_ms_per_plan` the sum of the kernels' HIP-event times of one plan
-(the paper's T_GPU).
+(the paper's T_GPU), from a pass with timing on: counts and depth tables, one
+launch otherwise, are then launched one after the other so that each has a
+time (`kernel_ms`).
 
 Printed as one JSON line.  Besides the contract fields it carries
 `roofline` (the fill kernel: 8 bytes written per nonzero over its

@@ -496,9 +496,10 @@ void fspb_surrogate_destroy(fspb_surrogate *sur);
 /*
  * dose[i] = sum_j w[j] D_ij.  indptr (n_rows + 1), indices, values, w (n_rows)
  * and dose (n_voxels) are DEVICE pointers; dose is overwritten.  Neighbouring
- * rows are summed together and the sums added with FP32 atomics, so the
- * rounding of each voxel's sum depends on the order in which they land (the value itself is the same to FP32
- * precision; fspb_voxel_dose is the bit-reproducible form).  Entries whose
+ * long rows are summed together; the sums, and the entries of short rows, are
+ * added with FP32 atomics, so the rounding of each voxel's sum depends on the
+ * order in which they land (the value itself is the same to FP32 precision;
+ * fspb_voxel_dose is the bit-reproducible form).  Entries whose
  * column lies outside [0, n_voxels) are skipped.  indices and values are
  * read only where indptr says there are entries (they may be NULL for a
  * matrix without any).

@@ -579,7 +579,8 @@ __device__ void count_beamlet_wide(const PlanDev &P, int j, int *s_tile)
  * below n_count count (WIDE: a beamlet each, else one per wave), the others trace a beamlet per
  * wave.  Both are chains of latency (grid rows in steps of 128, crossings in FP64) and together
  * hide each other's: 64^3 plan of 100 beamlets 59 -> 41 us (one wave per count, a launch each: 20
- * and 10 us of it), 9 x 576 on 256x256x100 1355 -> 1335.
+ * and 10 us of it); mask, counts and tables of 9 x 576 on 256x256x100 191 -> 140, of 9 x 900 on 128^3
+ * 160 -> 125 (WIDE 163 and 156).
  */
 template <bool WIDE>
 __global__ __launch_bounds__(kBlock) void k_trace(const PlanDev *__restrict__ plans, int n_count)
@@ -844,8 +845,9 @@ constexpr float is_scale = EM >= 3 ? kIsScale / kNormUnit : kIsScale;
  * serves r = sigma' q, isk = t' q and u isk = U' q, and the other terms' are fixed
  * multiples of it.  With the paired erf lookups the slab's fill issues 81 VALU
  * instructions per 64 nonzeros instead of 88, one of them a reciprocal instead of
- * three.  The card's power limit then sets the pace (the clock moves between
- * 2.0 and 2.4 GHz over a fill): pelvis fill 1119 -> 1085 us, slab fill 1765 -> 1763.
+ * three: pelvis fill 1119 -> 1085 us, slab fill 1765 -> 1763, at a clock that falls with
+ * the load (2.09 GHz over the slab's fill, 2.35 over the pelvis', 2.40 in memory-bound
+ * kernels).
  */
 template <int K, bool GUARD, int EM, bool SURR>
 __device__ inline float dose_value(const FillConst<K> &c, const float2 *__restrict__ tab,
@@ -984,7 +986,7 @@ __device__ __attribute__((always_inline)) inline void fill_beamlet(const PlanDev
     constexpr int kB = W * kWave;
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = lane_id();
     constexpr bool SE = erf_mirrored_mode(EM);
-    // mode 3, analytic form: term weights relative to the first, whose weight the depth dose carries
+    // modes 3 and 4, analytic form: term weights relative to the first, whose weight the depth dose carries
     constexpr bool FOLD_W = EM >= 3 && !GEN;
     // the row start values' t' and the depth table in the tables' own coordinates (dose_value)
     constexpr bool UNITS = !SURR;
@@ -1757,10 +1759,11 @@ hipError_t launch_batch_fill(int K, int W, const PlanDev *const *plans, const Ou
 
 /*
  * Workgroups per beamlet of a plan's fill: with a workgroup each, a plan of few beamlets leaves
- * CUs idle or ends in a ragged last round (100 beamlets: fill 23 us in 6 parts against 53; 715 with
- * the three-term kernel: the whole plan 224 us in 5 parts against 268), while a plan of many gains
- * nothing and stages every table twice (5184 beamlets: 1.264 ms in 3 parts against 1.248, 1.434
- * in 10).  No more parts than a beamlet has sets of tiles.
+ * CUs idle or ends in a ragged last round (whole plans: 100 beamlets 36 us, 67 in one part; 715 with
+ * the three-term kernel 186 us in 7 parts, 240 in one, 191 in 4, 195 in 5, 197 in 10; 1080 on 128^3 295
+ * in 5, 372 in one, 311 in 3), while a plan of many gains nothing and stages every table twice (5184
+ * beamlets: the fill 1.264 ms in 3 parts against 1.248, 1.434 in 10).  No more parts than a beamlet has
+ * sets of tiles.
  */
 constexpr int kFillGroups = 5000;
 static unsigned fill_parts(const PlanDev &h, int n_rows)

@@ -166,7 +166,7 @@ __global__ __launch_bounds__(kBlock) void k_zero_u32(uint32_t *__restrict__ x, i
  * straight to memory).
  */
 constexpr int kDoseRows = 32;
-constexpr int kDoseWindow = 2048;              // 8 KB of LDS per wave: sixteen waves per CU
+constexpr int kDoseWindow = 2048;              // 8 KB of LDS per wave
 constexpr int kDoseSets = 4;                   // 64-entry sets whose loads are issued together
 constexpr int kDoseMinEntries = 64;            // windows pay with more entries than this each and at
 constexpr int kDoseSlack = 1024;               // least 4/3 per touched voxel, give or take a share's
@@ -554,12 +554,16 @@ __global__ __launch_bounds__(BLOCK) void k_fluence_gradient(const int64_t *__res
  * because many rows are shorter than a step of 16 or 32 (64x64x64, one beam of
  * 100: 8 us, 13 with 16 lanes, 25 with 32).  w comes from LDS where a CU can hold
  * four copies and so all its waves (128^3, 9 beams of 900: 1020 us, gathered
- * through the cache 1202; 12500 beamlets 117 and 102) and the matrix has a third of an entry for
- * each word copied (64^3, 8100 beamlets: with 2.5 entries per word 144 and 184, with 0.27 23.3 and
- * 18.9, with 0.02 13.5 and 7.6; 9000 on 2e6 voxels, 0.49: 102 and 87 where neighbouring voxels
- * meet the same beamlets, 105 and 158 where any), and workgroups stay for many rows: 8191 of them (the slab with 4095: 1082 us, 8191: 1028, 12287: 1016; a
- * pelvis 910, 896, 1016), an odd number, so that no workgroup's rows keep the same
- * place in the grid's lines (a pelvis with 8192: 1231).
+ * through the cache 1202; 12500 beamlets 117 and 102) and the matrix has a third of an
+ * entry for each word copied (64^3, 8100 beamlets: with 2.5 entries per word 144 and 184,
+ * with 0.27 23.3 and 18.9, with 0.02 13.5 and 7.6; 9000 on 2e6 voxels, 0.49: 102 and 87
+ * where neighbouring voxels meet the same beamlets, 105 and 158 where any).
+ *
+ * Workgroups stay for many rows: 8191 of them (128^3, 9 beams of 900 with 4095: 1082 us,
+ * 8191: 1028, 12287: 1016; 256x256x100, 9 beams of 576: 910, 896, 1016), an odd number, so
+ * that no workgroup's rows keep the same place in the grid's lines (that matrix with 8064
+ * 1095, with 8189, 8190, 8192 and 8193 908, 844, 1205 and 912; 9 beams of 1600 and a 1 cm
+ * cutoff 350 with the odd numbers, 493 with 8064, 531 with 8192; on 128^3 all within 4 %).
  * 128^3, 9 beams of 900, 6.5e8 entries: 1028 us (5.1 TB/s), 1469 with 16 lanes per
  * row, a workgroup per 16 rows, the tail after the steps and w from the cache;
  * 256x256x100, 9 beams of 576: 1916 -> 896.
@@ -1003,9 +1007,10 @@ static inline unsigned blocks_of(int64_t items, int per_block)
     return (unsigned)((items + per_block - 1) / per_block);
 }
 
-// Workgroups of the beamlet-row dose: one round of what is resident by LDS, four per CU (on the
-// 6.5e8-entry slab 1.55 ms against 1.66 with two rounds, whose shares are shorter and so less
-// aligned between rows).  Rows per group: 32, since the more rows share a voxel the fewer atomics;
+// Workgroups of the beamlet-row dose: four per CU in one round, though LDS (32 KB of 160) and registers
+// (88) admit five.  With 1280 of them shares are shorter and so less aligned between rows, and more
+// windows are open at once: the 6.5e8-entry slab 2.08 ms against 1.55, 256x256x100 with 9 beams of 576
+// 1.45 against 1.11 (two rounds of four: the slab 1.66).  Rows per group: 32, since the more rows share a voxel the fewer atomics;
 // with few rows 8, for enough waves (240 rows of 8e4 entries: 0.10 ms against 0.19 with 32; 900
 // rows: 0.22 against 0.17).
 constexpr unsigned kDoseGroups = 1024;
