@@ -426,7 +426,7 @@ typedef float vf4 __attribute__((ext_vector_type(4)));
  *
  * Bound by the read of D.  Rows start anywhere, so steps share cache lines: marked
  * as streamed the loads fetch them twice (128^3, 9 beams of 900, 8.1e4 entries a
- * row: 1027 us against 977).
+ * row, with groups of 16 rows as below: 1027 us against 977).
  *
  * The width follows the number of rows, all that the host knows of the matrix.  Few
  * rows get 1024 threads each, or most of the chip idles (240 rows of 8e4 entries:
@@ -435,17 +435,18 @@ typedef float vf4 __attribute__((ext_vector_type(4)));
  * 1024; of 1000: 18.1 and 31.6; at 2000 rows of 50 the widths are equal, at 4000
  * they take 7.8 and 10.2).  Long rows then need many entries in flight per lane, or
  * so many rows are open at once that r falls out of the L2: PER 8 takes 977 us on
- * that slab, PER 4 999, 1024 threads 948; above kGradMany rows, where rows are
- * shorter still, PER 4 (40000 of 2000: 119 us, PER 8 131).
+ * that slab, PER 4 999; above kGradMany rows, where rows are shorter still, PER 4
+ * (40000 of 2000: 119 us, PER 8 131).
  *
  * With 256 threads kGradXcd consecutive rows go to one XCD (workgroups are dealt to
- * the XCDs in turn), since neighbouring beamlets gather the same voxels of r: 977 us
- * on the slab, 1047 with the rows dealt one by one; groups of 64 take 960 there but
- * 642 against 626 on 256x256x100 with 9 beams of 576, of 256 994 and 699.
+ * the XCDs in turn), since neighbouring beamlets gather the same voxels of r.  That slab:
+ * 959 us (1024 threads a row 945, 256 as before them 1070), 977 in groups of 16, 1047
+ * one by one; groups of 64 take 960 but on 256x256x100 with 9 beams of 576 642 against 623,
+ * of 256 994 and 699.
  */
 constexpr int kGradFew = 2048;
 constexpr int kGradMany = 32768;
-constexpr int kGradXcd = 16;
+constexpr int kGradXcd = 32;
 template <int GROUP>
 __device__ inline int grad_row(int n_rows)
 {

@@ -9,7 +9,7 @@ STEPS = [1024, 2048, 4096]        # entries of a step: 256 threads by 4 or 8, 10
 EDGES = [0, 1, 255, 256, 257] + [m * s + d for s in STEPS for m in (1, 2) for d in (-1, 0, 1)] + [1024 + 1023, 6143, 9000]
 
 
-@pytest.mark.parametrize("rows", [2048, 2049, 2048 + 127, 2048 + 128, 32768, 32769])
+@pytest.mark.parametrize("rows", [2048, 2049, 2048 + 255, 2048 + 256, 32768, 32769])
 def test_gradient_is_the_fp64_sum(rows):
     import torch
     if not torch.cuda.is_available():
