@@ -112,7 +112,7 @@ __device__ inline uint32_t bf16_pair(float a, float b)
  * 16 samples.  Weights are read from LDS once for all four tiles.  Bound by the
  * 256 quarter-rate instructions of the 128 SiLUs per sample: the
  * surrogate fill of a pelvis plan (9 x 576 beamlets, 4.1e8 entries) takes 15.4 ms, 24.9 with
- * h1 and the results exchanged through LDS (1110 and 1529 vector instructions per 64 samples).
+ * h1 and the results exchanged through LDS (1125 and 1529 vector instructions per 64 entries).
  */
 template <bool FOLD>
 __device__ inline float forward_wave(const Weights &W, const W2Frags &wf, const float x[4])

@@ -1350,8 +1350,8 @@ typedef float vf4u __attribute__((ext_vector_type(4), aligned(4)));
  *
  * Bound by memory, and by how much of the output is open at a time: a column's
  * cache lines are written piece by piece and leave L2 half filled if too many
- * buckets are under way.  6.5e8 entries in 3.03 ms (6.9 GB fetched, since runs of
- * 18 entries share their lines with neighbours, and 6.2 written, 4.3 TB/s)
+ * buckets are under way.  6.5e8 entries in 3.03 ms (5.6 GB fetched, since runs of
+ * 18 entries share their lines with neighbours, and 5.7 written, 3.7 TB/s)
  * against 3.97 with each batch's entries reordered in LDS.
  */
 template <int W>
